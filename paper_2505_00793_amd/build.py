@@ -15,6 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmfmg.so")
+GEMM_PARTS = 8   # gemm.hip is compiled in parts (its kernel instances), side by side
 SOURCES = ["gemm.hip", "elementwise.hip", "transformer.hip", "attention.hip", "tf_engine.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -26,13 +27,20 @@ FLAGS = [
 ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+def _units(src: str):
+    """(object, extra flags) of each translation unit of a source."""
+    stem = os.path.join(BUILD_DIR, os.path.splitext(src)[0])
+    if src == "gemm.hip":
+        return [(f"{stem}_{k}.o", [f"-DGEMM_PART={k}"]) for k in range(GEMM_PARTS)]
+    return [(stem + ".o", [])]
+
+
+def _compile(job) -> None:
+    src, obj, extra = job
+    cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stderr}")
-    return obj
 
 
 def build(verbose: bool = True, only=None) -> str:
@@ -42,9 +50,10 @@ def build(verbose: bool = True, only=None) -> str:
     todo = SOURCES if not only else [s for s in SOURCES if s in only]
     if only and len(todo) != len(set(only)):
         raise ValueError(f"unknown sources in {only}; sources are {SOURCES}")
-    with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        list(ex.map(_compile, todo))
-    objs = [os.path.join(BUILD_DIR, os.path.splitext(s)[0] + ".o") for s in SOURCES]
+    jobs = [(s, obj, extra) for s in todo for obj, extra in _units(s)]
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        list(ex.map(_compile, jobs))
+    objs = [obj for s in SOURCES for obj, _ in _units(s)]
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

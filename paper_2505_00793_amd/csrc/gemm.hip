@@ -1591,9 +1591,7 @@ hipError_t gemm_param_and_act_bwd(const GemmOperands<T>& opw, int flags_w, const
       }
     }
   }
-  hipError_t r = gemm_param<T>(opw, flags_w, P, s);
-  if (r != hipSuccess) return r;
-  return gemm_act_bwd<T>(opd, flags_d, e, s);
+  return hipErrorInvalidValue;   // not a pair (gemm_pairs)
 }
 
 // Both tile kernels sum the bias entries of a parameter epilogue; split-K
@@ -1603,9 +1601,8 @@ bool gemm_fuses_bias(const GemmOperands<T>& op, int flags) {
   if (flags == 0 || op.batch != 1 || op.M <= 0 || op.N <= 0) return false;
   return !(op.ws && splitk_count(op.M, op.N, op.K) > 1);
 }
-template bool gemm_fuses_bias<bf16_t>(const GemmOperands<bf16_t>&, int);
-template bool gemm_fuses_bias<float>(const GemmOperands<float>&, int);
 
+#if !defined(GEMM_PART) || GEMM_PART == 0
 long gemm_splitk_floats(int M, int N, int K) {
   const int S = splitk_count(M, N, K);
   return S > 1 ? 2L * S * M * N : 0;
@@ -1615,6 +1612,7 @@ long gemm_splitk_fwd_f32_floats(int M, int N, int K) {
   const int S = splitk_count_small(M, N, K);
   return S > 1 ? 2L * S * M * N : 0;
 }
+#endif
 
 template <typename T>
 hipError_t gemm_act_fwd(const GemmOperands<T>& op, int flags, const EpiActFwd<T>& epi,
@@ -1651,24 +1649,43 @@ hipError_t gemm_head_split(const GemmOperands<T>& op, int flags, const EpiHeadSp
   return dispatch(op, flags, HeadSplitOp<T>{e, e.M, e.N}, s);
 }
 
-template hipError_t gemm_store<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiStore&, hipStream_t);
-template hipError_t gemm_store<float>(const GemmOperands<float>&, int, const EpiStore&, hipStream_t);
-template hipError_t gemm_resid<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiResid&, hipStream_t);
-template hipError_t gemm_resid<float>(const GemmOperands<float>&, int, const EpiResid&, hipStream_t);
-template hipError_t gemm_head_merge<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiHeadMerge<bf16_t>&, hipStream_t);
-template hipError_t gemm_head_merge<float>(const GemmOperands<float>&, int, const EpiHeadMerge<float>&, hipStream_t);
-template hipError_t gemm_head_split<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiHeadSplit<bf16_t>&, hipStream_t);
-template hipError_t gemm_head_split<float>(const GemmOperands<float>&, int, const EpiHeadSplit<float>&, hipStream_t);
-template hipError_t gemm_act_fwd<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiActFwd<bf16_t>&, hipStream_t);
-template hipError_t gemm_act_fwd<float>(const GemmOperands<float>&, int, const EpiActFwd<float>&, hipStream_t);
-template hipError_t gemm_act_bwd<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiActBwd<bf16_t>&, hipStream_t);
-template hipError_t gemm_act_bwd<float>(const GemmOperands<float>&, int, const EpiActBwd<float>&, hipStream_t);
+// Explicit instantiations.  The build compiles this file once per part (GEMM_PART = 0 .. 7), all
+// parts at once; without GEMM_PART one translation unit holds everything.
+#if !defined(GEMM_PART) || GEMM_PART == 0
 template hipError_t gemm_param<bf16_t>(const GemmOperands<bf16_t>&, int, const ParamArgs<bf16_t>&, hipStream_t);
-template hipError_t gemm_param<float>(const GemmOperands<float>&, int, const ParamArgs<float>&, hipStream_t);
-
+#endif
+#if !defined(GEMM_PART) || GEMM_PART == 1
+template hipError_t gemm_act_bwd<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiActBwd<bf16_t>&, hipStream_t);
+#endif
+#if !defined(GEMM_PART) || GEMM_PART == 2
+template hipError_t gemm_store<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiStore&, hipStream_t);
+template hipError_t gemm_resid<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiResid&, hipStream_t);
+#endif
+#if !defined(GEMM_PART) || GEMM_PART == 3
+template hipError_t gemm_act_fwd<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiActFwd<bf16_t>&, hipStream_t);
+#endif
+#if !defined(GEMM_PART) || GEMM_PART == 4
+template hipError_t gemm_store<float>(const GemmOperands<float>&, int, const EpiStore&, hipStream_t);
+template hipError_t gemm_resid<float>(const GemmOperands<float>&, int, const EpiResid&, hipStream_t);
+template hipError_t gemm_head_merge<float>(const GemmOperands<float>&, int, const EpiHeadMerge<float>&, hipStream_t);
+template hipError_t gemm_head_split<float>(const GemmOperands<float>&, int, const EpiHeadSplit<float>&, hipStream_t);
+#endif
+#if !defined(GEMM_PART) || GEMM_PART == 5
+template hipError_t gemm_head_merge<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiHeadMerge<bf16_t>&, hipStream_t);
+template hipError_t gemm_head_split<bf16_t>(const GemmOperands<bf16_t>&, int, const EpiHeadSplit<bf16_t>&, hipStream_t);
+template bool gemm_fuses_bias<bf16_t>(const GemmOperands<bf16_t>&, int);
 template bool gemm_pairs<bf16_t>(const GemmOperands<bf16_t>&, int, const GemmOperands<bf16_t>&, int);
-template bool gemm_pairs<float>(const GemmOperands<float>&, int, const GemmOperands<float>&, int);
 template hipError_t gemm_param_and_act_bwd<bf16_t>(const GemmOperands<bf16_t>&, int, const ParamArgs<bf16_t>&, const GemmOperands<bf16_t>&, int, const EpiActBwd<bf16_t>&, hipStream_t);
+#endif
+#if !defined(GEMM_PART) || GEMM_PART == 6
+template hipError_t gemm_act_fwd<float>(const GemmOperands<float>&, int, const EpiActFwd<float>&, hipStream_t);
+template hipError_t gemm_act_bwd<float>(const GemmOperands<float>&, int, const EpiActBwd<float>&, hipStream_t);
+#endif
+#if !defined(GEMM_PART) || GEMM_PART == 7
+template hipError_t gemm_param<float>(const GemmOperands<float>&, int, const ParamArgs<float>&, hipStream_t);
+template bool gemm_fuses_bias<float>(const GemmOperands<float>&, int);
+template bool gemm_pairs<float>(const GemmOperands<float>&, int, const GemmOperands<float>&, int);
 template hipError_t gemm_param_and_act_bwd<float>(const GemmOperands<float>&, int, const ParamArgs<float>&, const GemmOperands<float>&, int, const EpiActBwd<float>&, hipStream_t);
+#endif
 
 }  // namespace mfmg

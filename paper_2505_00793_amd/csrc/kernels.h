@@ -203,9 +203,9 @@ hipError_t gemm_param(const GemmOperands<T>& op, int flags, const ParamArgs<T>& 
                       hipStream_t s);
 // A layer's backward-weight product (with the parameter epilogue) and its
 // backward-data product (with the activation epilogue), which are independent:
-// one launch running both when they are small (bf16 operands on 64-row tiles,
-// at most two workgroups per compute unit together), else the two launches
-// above in that order.
+// gemm_pairs says whether both are small enough to share one launch (bf16
+// operands on 64-row tiles, at most two workgroups per compute unit together),
+// which gemm_param_and_act_bwd then makes.
 template <typename T>
 bool gemm_pairs(const GemmOperands<T>& opw, int flags_w, const GemmOperands<T>& opd, int flags_d);
 template <typename T>
