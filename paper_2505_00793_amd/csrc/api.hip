@@ -87,14 +87,14 @@ struct mfmg_problem {
            d.precision == MFMG_PREC_FP32 && linreg_fits(T, d.rows, d.val_rows, w[0]);
   }
   int maxR() const { return d.rows > d.val_rows ? d.rows : d.val_rows; }
-  // Contraction of the last layer's backward-data product (over its outputs):
-  // with bf16 operands the width rounded up to 8, so that the product takes the
-  // direct-to-LDS path; the loss head writes the padding columns of dZ as zero
-  // and zero_last_pads clears those of the W copies.
-  int k_last() const {
-    const int c = w[L];
-    return bf16() && L >= 2 && c % 8 != 0 ? (c + 7) / 8 * 8 : c;
-  }
+  // Length of a contraction over n elements of operand rows: with bf16 operands
+  // n rounded up to their 16-byte chunks, so that every product takes the
+  // direct-to-LDS path whatever its widths and rows are.  The rows' padding is
+  // zero: the producers of activations and gradients write it with each row, and
+  // zero_pads clears that of the weights' copies once per call.  (A 781-1000-515-37
+  // ReLU network, 250 rows, T = 4: 1.92 ms with the ragged products on the
+  // register-staged kernel's single-element loads, 0.65 ms padded.)
+  int kx(int n) const { return bf16() ? (int)ld(n) : n; }
 };
 
 namespace {
@@ -361,7 +361,7 @@ struct Eng {
   mfmg_status load_x(const float* x, int R, const Act<T>& a) {
     TimingScope ts(7, s);
     HIPCHK(convert_matrix<T>(x, R, p->w[0], p->w[0], a.X, (int)p->ld(p->w[0]), a.XT,
-                             (int)p->ld(R), s));
+                             (int)p->ld(R), s, 1, 0, 0, 0, 1));
     return MFMG_OK;
   }
 
@@ -377,7 +377,7 @@ struct Eng {
       op.lda = op.ldb = (int)p->ld(nin);
       op.M = R;
       op.N = nout;
-      op.K = nin;
+      op.K = p->kx(nin);
       op.ws = a.skws;
       op.ws_floats = a.skws_n;
       const int flags = G_C1 | (dual ? (G_BD | (l > 0 ? G_AD : 0)) : 0);
@@ -397,6 +397,7 @@ struct Eng {
       e.AdoT = a.AdT[l];
       e.ldA = (int)p->ld(nout);
       e.ldAT = (int)p->ld(R);
+      e.zpad = e.ldA != nout || e.ldAT != R;
       TimingScope ts(dual ? 3 : 0, s);
       HIPCHK(gemm_act_fwd<T>(op, flags, e, s));
     }
@@ -424,7 +425,7 @@ struct Eng {
     la.ddT = a.dZdT[0];
     la.ld = (int)p->ld(C);
     la.ldT = (int)p->ld(R);
-    la.pad_to = p->k_last();
+    la.pad_to = p->kx(C);
     la.loss_rows = a.loss_rows;
     la.mvp_rows = mvp_rows;
     la.deta_rows = deta_rows;
@@ -459,7 +460,7 @@ struct Eng {
       opw.lda = opw.ldb = (int)p->ld(R);
       opw.M = nin;
       opw.N = nout;
-      opw.K = R;
+      opw.K = p->kx(R);
       const int flags_w = (need_c1 ? G_C1 : 0) | (dual ? (G_BD | (l > 0 ? G_AD : 0)) : 0);
       // backward-data product dA = dZ W^T (and its tangent), activation epilogue
       GemmOperands<T> opd;
@@ -473,7 +474,7 @@ struct Eng {
         opd.lda = opd.ldb = (int)p->ld(nout);
         opd.M = R;
         opd.N = nin;
-        opd.K = l == p->L - 1 ? p->k_last() : nout;
+        opd.K = p->kx(nout);
         e.Zp = a.Z[l - 1];
         e.Zdp = a.Zd[l - 1];
         e.Ap = a.A[l - 1];
@@ -488,6 +489,7 @@ struct Eng {
         e.dZdT = a.dZdT[cur ^ 1];
         e.ld = (int)p->ld(nin);
         e.ldT = (int)p->ld(R);
+        e.zpad = e.ld != nin || e.ldT != R;
       }
       // the bias entries: summed by the backward-weight GEMM itself unless it
       // runs split-K, else by a reduction over dZ^T
@@ -523,29 +525,33 @@ struct Eng {
     if (st_ != MFMG_OK) return st_;      \
   } while (0)
 
-// Columns w[L] .. k_last() - 1 of the last layer's W copies (the B operand of
-// its backward-data product) set to zero in every operand set of a call;
-// nothing else writes there, so they stay zero for the whole call.
+// The padding of every weight copy's rows (columns nout .. ld - 1 of W, nin .. ld
+// - 1 of W^T) set to zero in every operand set of a call; nothing else writes
+// there, so it stays zero for the whole call.  bf16 operands only (see kx).
 template <typename T>
-mfmg_status zero_last_pads(const mfmg_problem* p, const std::vector<const OperandSet<T>*>& sets,
-                           hipStream_t s) {
-  const int l = p->L - 1, nout = p->w[p->L], kp = p->k_last();
-  if (kp == nout) return MFMG_OK;
+mfmg_status zero_pads(const mfmg_problem* p, const std::vector<const OperandSet<T>*>& sets,
+                      hipStream_t s) {
+  if (!p->bf16()) return MFMG_OK;
   ZeroColJobs J;
   J.n = 0;
-  for (const OperandSet<T>* o : sets) {
-    if (!o || !o->W[l]) continue;
+  auto add = [&](T* q, int rows, int cols) -> mfmg_status {
+    if (!q || p->ld(cols) == cols) return MFMG_OK;
     if (J.n == ZC_MAX_JOBS) {
       HIPCHK(zero_cols(J, s));
       J.n = 0;
     }
-    J.p[J.n] = reinterpret_cast<uint16_t*>(o->W[l]);
-    J.rows[J.n] = p->w[l];
-    J.ld[J.n] = (int)p->ld(nout);
-    J.c0[J.n] = nout;
-    J.c1[J.n] = kp;
+    J.p[J.n] = reinterpret_cast<uint16_t*>(q);
+    J.rows[J.n] = rows;
+    J.ld[J.n] = J.c1[J.n] = (int)p->ld(cols);
+    J.c0[J.n] = cols;
     ++J.n;
-  }
+    return MFMG_OK;
+  };
+  for (const OperandSet<T>* o : sets)
+    for (int l = 0; o && l < p->L; ++l) {
+      TRY(add(o->W[l], p->w[l], p->w[l + 1]));
+      TRY(add(o->WT[l], p->w[l + 1], p->w[l]));
+    }
   if (J.n) HIPCHK(zero_cols(J, s));
   return MFMG_OK;
 }
@@ -589,7 +595,7 @@ mfmg_status run_meta(const mfmg_problem* p, const float* theta0, const float* op
     for (const OperandSet<T>& o : mp.slot) sets.push_back(&o);
     sets.push_back(&mp.v[0]);
     if (!p->adam()) sets.push_back(&mp.v[1]);
-    TRY(zero_last_pads<T>(p, sets, s));
+    TRY(zero_pads<T>(p, sets, s));
   }
   const bool adam = p->adam();
   const bool wlog = p->d.meta == MFMG_META_EXAMPLE_WEIGHT_LOGITS;
@@ -801,7 +807,7 @@ mfmg_status run_inner_step(const mfmg_problem* p, const float* theta, const floa
   StepPlan<T> sp;
   plan_step(p, ws, sp);
   Eng<T> E{p, s};
-  TRY(zero_last_pads<T>(p, {&sp.th}, s));
+  TRY(zero_pads<T>(p, {&sp.th}, s));
   const int R = (int)b->rows;
   const long n = p->n_theta;
   const float* alpha =
@@ -833,7 +839,7 @@ mfmg_status run_hvp(const mfmg_problem* p, const float* theta, const float* eta,
   StepPlan<T> sp;
   plan_step(p, ws, sp);
   Eng<T> E{p, s};
-  TRY(zero_last_pads<T>(p, {&sp.th, &sp.v}, s));
+  TRY(zero_pads<T>(p, {&sp.th, &sp.v}, s));
   const int R = (int)b->rows;
   const float* alpha =
       p->d.meta == MFMG_META_EXAMPLE_WEIGHT_LOGITS ? eta + (long)step * p->d.rows : nullptr;

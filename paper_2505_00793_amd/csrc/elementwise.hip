@@ -45,20 +45,19 @@ __global__ void __launch_bounds__(256) convert_kernel(ConvJobs<T> J, int batch, 
   T* dst = P.dst;
   T* dstT = P.dstT;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  const int cols_w = J.zpad ? ldd : cols, rows_w = J.zpad ? lddT : rows;   // written
   for (int i = ty; i < 64; i += 4) {
     const int r = r0 + i, c = c0 + tx;
     float v = 0.0f;
-    if (r < rows && c < cols) {
-      v = src[(long)r * lds + c];
-      if (dst) dst[(long)r * ldd + c] = Elem<T>::from_float(v);
-    }
+    if (r < rows && c < cols) v = src[(long)r * lds + c];
+    if (dst && r < rows && c < cols_w) dst[(long)r * ldd + c] = Elem<T>::from_float(v);
     tile[i][tx] = v;
   }
   if (!dstT) return;
   __syncthreads();
   for (int i = ty; i < 64; i += 4) {
     const int c = c0 + i, r = r0 + tx;
-    if (c < cols && r < rows) dstT[(long)c * lddT + r] = Elem<T>::from_float(tile[tx][i]);
+    if (c < cols && r < rows_w) dstT[(long)c * lddT + r] = Elem<T>::from_float(tile[tx][i]);
   }
 }
 
@@ -78,6 +77,7 @@ __global__ void __launch_bounds__(256) convert_vec_kernel(ConvJobs<T> J, int bat
   T* dstT = P.dstT;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const int c = c0 + tx * 4;
+  const int cols_w = J.zpad ? ldd : cols, rows_w = J.zpad ? lddT : rows;   // written
   if ((cols & 3) == 0) {
     // every 16-byte chunk lies wholly inside or outside the matrix: the thread's
     // four rows are requested at once, from indices clamped into it, and the
@@ -93,7 +93,7 @@ __global__ void __launch_bounds__(256) convert_vec_kernel(ConvJobs<T> J, int bat
       const int i = ty + 16 * it, r = r0 + i;
       const bool in = r < rows && c < cols;
       const float4 v = in ? x[it] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      if (in && dst) store4(dst + (long)r * ldd + c, v.x, v.y, v.z, v.w);
+      if (dst && r < rows && c < cols_w) store4(dst + (long)r * ldd + c, v.x, v.y, v.z, v.w);
       *reinterpret_cast<float4*>(&tile[i][tx * 4]) = v;
     }
   } else {
@@ -108,8 +108,8 @@ __global__ void __launch_bounds__(256) convert_vec_kernel(ConvJobs<T> J, int bat
         } else {
 #pragma unroll
           for (int k = 0; k < 4; ++k)
-            if (c + k < cols) {
-              v[k] = src[(long)r * lds + c + k];
+            if (c + k < cols_w) {
+              if (c + k < cols) v[k] = src[(long)r * lds + c + k];
               if (dst) dst[(long)r * ldd + c + k] = Elem<T>::from_float(v[k]);
             }
         }
@@ -122,16 +122,16 @@ __global__ void __launch_bounds__(256) convert_vec_kernel(ConvJobs<T> J, int bat
   const int r = r0 + tx * 4;
   for (int j = ty; j < 64; j += 16) {
     const int cc = c0 + j;
-    if (cc >= cols || r >= rows) continue;
+    if (cc >= cols || r >= rows_w) continue;
     const float w0 = tile[tx * 4][j], w1 = tile[tx * 4 + 1][j], w2 = tile[tx * 4 + 2][j],
                 w3 = tile[tx * 4 + 3][j];
-    if (r + 4 <= rows) {
+    if (r + 4 <= rows_w) {
       store4(dstT + (long)cc * lddT + r, w0, w1, w2, w3);
     } else {
       const float w[4] = {w0, w1, w2, w3};
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        if (r + k < rows) dstT[(long)cc * lddT + r + k] = Elem<T>::from_float(w[k]);
+        if (r + k < rows_w) dstT[(long)cc * lddT + r + k] = Elem<T>::from_float(w[k]);
     }
   }
 }
@@ -156,7 +156,9 @@ __global__ void __launch_bounds__(256) transpose_kernel(const T* __restrict__ a0
   __syncthreads();
   for (int i = ty; i < 64; i += 4) {
     const int c = c0 + i, r = r0 + tx;
-    if (c < cols && r < rows) dst[(long)c * ldT + r] = Elem<T>::from_float(tile[tx][i]);
+    // past rows the tile is zero: the row's padding up to a multiple of 8
+    if (c < cols && r < min(ldT, (rows + 7) / 8 * 8))
+      dst[(long)c * ldT + r] = Elem<T>::from_float(tile[tx][i]);
   }
 }
 
@@ -273,6 +275,14 @@ __global__ void __launch_bounds__(256) loss_kernel(LossArgs<T> a) {
   if (C + lane < a.pad_to) {
     a.d[(long)row * a.ld + C + lane] = Elem<T>::from_float(0.0f);
     if (a.dual) a.dd[(long)row * a.ld + C + lane] = Elem<T>::from_float(0.0f);
+  }
+  if (a.direct_t && row == a.rows - 1) {   // the padding of the transposed rows
+    const int re = min(a.ldT, (a.rows + 7) / 8 * 8);
+    for (int c = lane; c < C; c += 64)
+      for (int r = a.rows; r < re; ++r) {
+        a.dT[(long)c * a.ldT + r] = Elem<T>::from_float(0.0f);
+        if (a.dual) a.ddT[(long)c * a.ldT + r] = Elem<T>::from_float(0.0f);
+      }
   }
   const float* z = a.Z + (long)row * C;
   const float* zd = a.dual ? a.Zd + (long)row * C : nullptr;
@@ -1290,6 +1300,10 @@ hipError_t convert_matrices(const ConvJobs<T>& J, int rows, int cols, int lds, i
   if (rows <= 0 || cols <= 0 || batch <= 0 || J.n == 0) return hipSuccess;
   for (int k = 0; k < J.n; ++k)
     if (!J.src[k]) return hipErrorInvalidValue;
+  // the tiles of the grid must cover the padding
+  if (J.zpad && (ldd < cols || ldd - cols >= 16 / (int)sizeof(T) || ldd > cdiv(cols, 64) * 64 ||
+                 lddT < rows || lddT - rows >= 16 / (int)sizeof(T) || lddT > cdiv(rows, 64) * 64))
+    return hipErrorInvalidValue;
   dim3 grid(cdiv(cols, 64), cdiv(rows, 64), batch * J.n);
   const auto al = [](const void* q, uintptr_t a) { return (reinterpret_cast<uintptr_t>(q) % a) == 0; };
   const uintptr_t aw = 4 * sizeof(T);  // alignment of 4 elements
@@ -1334,9 +1348,10 @@ hipError_t transpose_bf16(const bf16_t* a0, const bf16_t* a1, int rows, int cols
 template <typename T>
 hipError_t convert_matrix(const float* src, int rows, int cols, int lds, T* dst, int ldd,
                           T* dstT, int lddT, hipStream_t s, int batch, long s_src, long s_dst,
-                          long s_dstT) {
+                          long s_dstT, int zpad) {
   ConvJobs<T> J;
   J.n = 1;
+  J.zpad = zpad;
   J.src[0] = src;
   J.dst[0] = dst;
   J.dstT[0] = dstT;
@@ -1462,8 +1477,8 @@ hipError_t linreg_meta_grad(const float* theta0, const float* eta, const float* 
 
 template hipError_t convert_matrices<bf16_t>(const ConvJobs<bf16_t>&, int, int, int, int, int, hipStream_t, int, long, long, long);
 template hipError_t convert_matrices<float>(const ConvJobs<float>&, int, int, int, int, int, hipStream_t, int, long, long, long);
-template hipError_t convert_matrix<bf16_t>(const float*, int, int, int, bf16_t*, int, bf16_t*, int, hipStream_t, int, long, long, long);
-template hipError_t convert_matrix<float>(const float*, int, int, int, float*, int, float*, int, hipStream_t, int, long, long, long);
+template hipError_t convert_matrix<bf16_t>(const float*, int, int, int, bf16_t*, int, bf16_t*, int, hipStream_t, int, long, long, long, int);
+template hipError_t convert_matrix<float>(const float*, int, int, int, float*, int, float*, int, hipStream_t, int, long, long, long, int);
 template hipError_t bias_reduce<bf16_t>(const bf16_t*, const bf16_t*, int, int, const ParamArgs<bf16_t>&, hipStream_t);
 template hipError_t bias_reduce<float>(const float*, const float*, int, int, const ParamArgs<float>&, hipStream_t);
 template hipError_t loss_head<bf16_t>(const LossArgs<bf16_t>&, hipStream_t);

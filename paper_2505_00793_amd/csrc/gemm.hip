@@ -142,6 +142,31 @@ __device__ __forceinline__ void store_row4(T* p, long off, int cnt, const float*
   }
 }
 
+// Columns n .. ld - 1 of row r (a row's padding) set to zero.
+template <typename T>
+__device__ __forceinline__ void zero_tail(T* p, long r, int n, int ld) {
+  for (; n < ld; ++n) p[r * ld + n] = Elem<T>::from_float(0.0f);
+}
+// The padding of the operand rows a tile completes, so that a product may
+// contract over whole 16-byte chunks: of the row-major outputs when the tile
+// holds the last columns, of the transposed ones when it holds the last rows.
+// After the walk, not inside it: a branch per row there kept the compiler from
+// overlapping the rows of the unpadded products (8 x 4096 network 2 % slower).
+template <typename T>
+__device__ __forceinline__ void zero_tile_pads(T* p, T* pd, int ld, T* pT, T* pdT, int ldT, int M,
+                                               int N, int m0, int rows, int n0, int cols) {
+  if (n0 + cols >= N && ld != N)
+    for (int m = m0 + threadIdx.x; m < min(m0 + rows, M); m += blockDim.x) {
+      zero_tail(p, m, N, ld);
+      if (pd) zero_tail(pd, m, N, ld);
+    }
+  if (m0 + rows >= M && ldT != M)
+    for (int n = n0 + threadIdx.x; n < min(n0 + cols, N); n += blockDim.x) {
+      zero_tail(pT, n, M, ldT);
+      if (pdT) zero_tail(pdT, n, M, ldT);
+    }
+}
+
 template <typename T>
 struct ActFwdOp {
   EpiActFwd<T> e;
@@ -179,6 +204,11 @@ struct ActFwdOp {
   __device__ __forceinline__ void trans(int k, int bz, int n, int m, int cnt,
                                         const float* v) const {
     store_row4(k == 0 ? e.AoT : e.AdoT, (long)n * e.ldAT + m, cnt, v);
+  }
+  __device__ __forceinline__ void pads(int m0, int rows, int n0, int cols) const {
+    if (e.zpad && !e.last)
+      zero_tile_pads(e.Ao, e.dual ? e.Ado : nullptr, e.ldA, e.AoT, e.dual ? e.AdoT : nullptr,
+                     e.ldAT, M, N, m0, rows, n0, cols);
   }
 };
 
@@ -289,6 +319,11 @@ struct ActBwdOp {
                                         const float* v) const {
     store_row4(k == 0 ? e.dZT : e.dZdT, (long)n * e.ldT + m, cnt, v);
   }
+  __device__ __forceinline__ void pads(int m0, int rows, int n0, int cols) const {
+    if (e.zpad)
+      zero_tile_pads(e.dZ, e.dual ? e.dZd : nullptr, e.ld, e.dZT, e.dual ? e.dZdT : nullptr, e.ldT,
+                     M, N, m0, rows, n0, cols);
+  }
 };
 
 template <typename T>
@@ -366,6 +401,10 @@ struct ParamOp {
   }
 };
 
+// Epilogues whose operand outputs may have padding to clear (see zero_tile_pads).
+template <class E> struct HasPads : std::false_type {};
+template <typename T> struct HasPads<ActFwdOp<T>> : std::true_type {};
+template <typename T> struct HasPads<ActBwdOp<T>> : std::true_type {};
 template <class E> struct IsParamOp : std::false_type {};
 template <typename T> struct IsParamOp<ParamOp<T>> : std::true_type {};
 template <class E> struct IsActFwdOp : std::false_type {};
@@ -613,7 +652,7 @@ __device__ __forceinline__ void walk_tile(float* S1, float* S2, int mr0, int n0,
       walked = true;
     }
   }
-  if constexpr (Epi::PRELOAD && NT == 256) {
+  if constexpr (Epi::PRELOAD && (NT == 256 || RP <= 64)) if (!walked) {
     // Any tile: every row's inputs first (single elements from clamped indices,
     // no branch around a load), then the rows inside the output.
     constexpr int TPR = BN / 4;
@@ -692,6 +731,7 @@ __device__ __forceinline__ void walk_tile(float* S1, float* S2, int mr0, int n0,
       }
     }
   }
+  if constexpr (HasPads<Epi>::value) epi.pads(mr0, RP, n0, BN);
   __syncthreads();
 }
 
@@ -1409,6 +1449,7 @@ __global__ void __launch_bounds__(256) splitk_epilogue(const float* __restrict__
     }
     epi.row(0, m, n, cn, c1, c2, t1, t2);
   }
+  if constexpr (HasPads<Epi>::value) epi.pads(m0, 16, n0, 64);
   const int nT = epi.n_trans();
   if (nT == 0) return;
 #pragma unroll
@@ -1502,16 +1543,18 @@ hipError_t launch_sized(const GemmOperands<T>& op, const Epi& epi, hipStream_t s
   return launch<T, FLAGS, 64, 64>(op, epi, s);
 }
 
+// The products each epilogue comes with; other flags are refused.
 template <typename T, class Epi>
 hipError_t dispatch(const GemmOperands<T>& op, int flags, const Epi& epi, hipStream_t s) {
-  switch (flags) {
-    case G_C1: return launch_sized<T, G_C1>(op, epi, s);
-    case G_C1 | G_BD: return launch_sized<T, G_C1 | G_BD>(op, epi, s);
-    case G_C1 | G_AD | G_BD: return launch_sized<T, G_C1 | G_AD | G_BD>(op, epi, s);
-    case G_AD | G_BD: return launch_sized<T, G_AD | G_BD>(op, epi, s);
-    case G_BD: return launch_sized<T, G_BD>(op, epi, s);
-    default: return hipErrorInvalidValue;
+  if (flags == G_C1) return launch_sized<T, G_C1>(op, epi, s);
+  if (flags == (G_C1 | G_AD | G_BD)) return launch_sized<T, G_C1 | G_AD | G_BD>(op, epi, s);
+  if constexpr (IsActFwdOp<Epi>::value || IsParamOp<Epi>::value)   // a first layer
+    if (flags == (G_C1 | G_BD)) return launch_sized<T, G_C1 | G_BD>(op, epi, s);
+  if constexpr (IsParamOp<Epi>::value) {   // an Adam reverse
+    if (flags == (G_AD | G_BD)) return launch_sized<T, G_AD | G_BD>(op, epi, s);
+    if (flags == G_BD) return launch_sized<T, G_BD>(op, epi, s);
   }
+  return hipErrorInvalidValue;
 }
 
 // The tile launch_sized picks for a bf16 product on the direct-to-LDS path:

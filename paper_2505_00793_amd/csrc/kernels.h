@@ -64,6 +64,8 @@ struct EpiActFwd {
   T* Ao;  T* AoT;        // [M][ldA], [N][ldAT]
   T* Ado; T* AdoT;       // (dual)
   int ldA, ldAT;
+  int zpad = 0;          // 1: columns N .. ldA - 1 (and M .. ldAT - 1) written as zero; both
+                         // paddings shorter than 16 bytes
 };
 
 // Backward-data of one layer: C1 = dA of the previous layer's output, C2 its
@@ -82,6 +84,7 @@ struct EpiActBwd {
   T* dZ;  T* dZT;        // [M][ld], [N][ldT]
   T* dZd; T* dZdT;
   int ld, ldT;
+  int zpad = 0;          // as in EpiActFwd, for ld and ldT
 };
 
 // What the per-parameter epilogue does with (g, hv) = (C1, C2) of a
@@ -186,6 +189,7 @@ struct LossArgs {
   T* dd; T* ddT;            // its tangent (dual)
   int ld, ldT;
   int pad_to;               // columns C .. pad_to - 1 of d (dd) are written as zero
+                            // (and rows rows .. roundup8(rows) - 1 of dT, up to ldT)
   int direct_t;             // set by loss_head: the kernel also writes dT (ddT) itself
   float* loss_rows;         // l_n (unweighted), or null
   float* mvp_rows;          // (1/N) ldot_n, or null
@@ -228,7 +232,7 @@ hipError_t gemm_head_split(const GemmOperands<T>& op, int flags, const EpiHeadSp
 template <typename T>
 hipError_t convert_matrix(const float* src, int rows, int cols, int lds, T* dst, int ldd,
                           T* dstT, int lddT, hipStream_t s, int batch = 1, long s_src = 0,
-                          long s_dst = 0, long s_dstT = 0);
+                          long s_dst = 0, long s_dstT = 0, int zpad = 0);
 
 // The same for up to CONV_MAX_JOBS matrices of one shape and layout in one
 // launch (job k: src[k] -> dst[k], dstT[k]; src[k] non-null).
@@ -239,6 +243,8 @@ struct ConvJobs {
   const float* src[CONV_MAX_JOBS] = {};
   T* dst[CONV_MAX_JOBS] = {};
   T* dstT[CONV_MAX_JOBS] = {};
+  int zpad = 0;   // 1: columns cols .. ldd - 1 of dst and rows .. lddT - 1 of dstT written as
+                  // zero (leading dimensions rounded up by less than 16 bytes)
 };
 // Transposed copies of bf16 matrices: up to TR_MAX_JOBS of one shape, each a
 // batch of matrices at strides s_src / s_dst (rows, leading dimensions and
@@ -311,7 +317,7 @@ hipError_t fill(float* p, long n, float v, hipStream_t s);
 
 // Zero columns c0 .. c1 - 1 (c1 <= ld) of up to ZC_MAX_JOBS bf16 matrices in one
 // launch (a fill kernel, no memset node).
-constexpr int ZC_MAX_JOBS = 48;
+constexpr int ZC_MAX_JOBS = 128;
 struct ZeroColJobs {
   int n;
   uint16_t* p[ZC_MAX_JOBS];

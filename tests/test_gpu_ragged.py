@@ -1,0 +1,37 @@
+"""bf16 products whose contractions are padded to whole 16-byte chunks: widths and rows of every
+residue modulo 8, in a workspace full of NaN, against the oracle's bf16 emulation."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from helpers import desc_of, group_errors, to_device, tol_of
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # widths, rows, val_rows, optimiser family
+    ((65, 130, 67, 3), 60, 43, W.C5), ((61, 35, 44, 5), 121, 129, W.C5),
+    ((9, 1, 7, 2), 3, 1, W.C5), ((70, 131, 6), 37, 64, W.C3), ((64, 128, 136), 65, 8, W.C5),
+    ((66, 257), 127, 130, W.C5),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c[0])))
+def test_padded_contractions(case):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2505_00793_amd import _lib as M
+    widths, rows, val_rows, base = case
+    cfg = base.with_(name="ragged", cfg_id=140, widths=widths, rows=rows, val_rows=val_rows, T=2)
+    inp = W.make_inputs(cfg)
+    dev = to_device(inp)
+    P = M.Problem(desc_of(cfg))
+    ws = P.workspace(P.mfmg_query_sizes(cfg.T).workspace_bytes)
+    ws.fill_(255)   # every float32 and bfloat16 in it is NaN
+    d = torch.empty(W.n_eta(cfg), device="cuda")
+    P.mfmg_meta_grad(dev["theta0"], dev["opt_state0"], dev["eta"], dev["xs"], dev["ys"], dev["vx"],
+                     dev["vy"], d, ws=ws)
+    ref, _ = oracle.meta_grad(cfg, inp, bf16=True)
+    errs = group_errors(cfg, d.cpu().numpy().astype(np.float64), ref)
+    assert max(errs) <= tol_of(cfg), errs
