@@ -620,21 +620,22 @@ __global__ void __launch_bounds__(1024) adam_reduce_kernel(const float* __restri
 // g = (2/N) X^T r, H v = (2/N) X^T rdot.
 // 512 threads.  The batches are used in the order of the sweep: the T
 // training batches, the validation batch, then the training batches again in
-// reverse.  Each is staged in LDS (when it fits in 80 KB) with rows padded to a
+// reverse.  Only batches small against d x d come here (linreg_meta_grad), so
+// each fits in LDS (80 KB); it is staged there with rows padded to a
 // pitch of 16 (mod 32) floats, so that the four rows a quarter-wave reads with
 // 16-byte accesses fall on distinct banks; the next batch's values are loaded
 // into registers while the current one is used, so the sweep waits on global
 // memory only for the first.  The checkpoints theta_t stay in LDS when
 // (T + 1) d <= 4096.  Residuals take four threads per row (every fourth 16-byte
-// group of the row, then a sum over the four lanes), X^T r takes 64 features x
-// 8 row groups per pass with an ordered sum of the 8 partials.
+// group of the row, then a sum over the four lanes), X^T r takes 16-byte column
+// groups x 32 row groups per pass with an ordered sum of the 32 partials.
 // ------------------------------------------------------------------------------------
 constexpr int LR_MAXD = 256;
 constexpr int LR_MAXR = 1024;
 constexpr int LR_MAXT = 64;
 constexpr int LR_THREADS = 512;
-constexpr int LR_RG = LR_THREADS / 64;   // row groups of the column pass
-constexpr int LR_YPT = LR_MAXR / LR_THREADS;  // targets per thread
+constexpr int LR_DIRECT_D = 224, LR_DIRECT_ROWS = 64;   // rows of a batch linreg_kernel takes
+static_assert(LR_DIRECT_ROWS <= LR_THREADS, "one target per thread");
 constexpr int LR_STAGE = 20480;  // floats of one batch staged in LDS, rows padded (80 KB)
 constexpr int LR_PF = LR_STAGE / LR_THREADS;  // prefetched floats per thread (n <= LR_STAGE)
 constexpr int LR_PF4 = LR_PF / 4;             // prefetched 16-byte groups per thread
@@ -659,9 +660,7 @@ __host__ __device__ __forceinline__ int lr_spitch(int d) {
   const int p = (d + 3) & ~3;
   return p + ((16 - (p & 31)) & 31);
 }
-__host__ __device__ __forceinline__ bool lr_staged(int rows, int d) {
-  return rows * lr_spitch(d) <= LR_STAGE;
-}
+static_assert(LR_DIRECT_ROWS * (LR_MAXD + 16) <= LR_STAGE, "every batch is staged");
 
 // Batch k of the sweep (k = 0 .. 2T).
 struct LrBatch {
@@ -682,27 +681,24 @@ __device__ __forceinline__ LrBatch lr_batch(const LinregArgs& a, int k) {
 // wait for every load in flight.
 struct LrRegs {
   float x[LR_PF];   // vec: group u in x[4u .. 4u + 3]
-  float y[LR_YPT];
+  float y;
 };
 template <bool VEC>
 __device__ __forceinline__ void lr_load(const LrBatch& b, int d, LrRegs& g) {
   const int tid = threadIdx.x;
-  if (lr_staged(b.rows, d)) {
-    const int n = b.rows * d;
-    if constexpr (VEC) {
-      const float4* X4 = reinterpret_cast<const float4*>(b.X);
+  const int n = b.rows * d;
+  if constexpr (VEC) {
+    const float4* X4 = reinterpret_cast<const float4*>(b.X);
 #pragma unroll
-      for (int u = 0; u < LR_PF4; ++u) {
-        const float4 v = X4[min(tid + u * LR_THREADS, n / 4 - 1)];
-        g.x[4 * u] = v.x; g.x[4 * u + 1] = v.y; g.x[4 * u + 2] = v.z; g.x[4 * u + 3] = v.w;
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < LR_PF; ++u) g.x[u] = b.X[min(tid + u * LR_THREADS, n - 1)];
+    for (int u = 0; u < LR_PF4; ++u) {
+      const float4 v = X4[min(tid + u * LR_THREADS, n / 4 - 1)];
+      g.x[4 * u] = v.x; g.x[4 * u + 1] = v.y; g.x[4 * u + 2] = v.z; g.x[4 * u + 3] = v.w;
     }
-  }
+  } else {
 #pragma unroll
-  for (int v = 0; v < LR_YPT; ++v) g.y[v] = b.y[min(tid + v * LR_THREADS, b.rows - 1)];
+    for (int u = 0; u < LR_PF; ++u) g.x[u] = b.X[min(tid + u * LR_THREADS, n - 1)];
+  }
+  g.y = b.y[min(tid, b.rows - 1)];
 }
 // Registers -> LDS (padded rows; the padding columns stay zero).  Callers
 // synchronise before (the previous batch's readers are done) and after.
@@ -710,10 +706,7 @@ template <bool VEC>
 __device__ __forceinline__ void lr_commit(const LrBatch& b, int d, const LrRegs& g, float* stage,
                                           float* ys) {
   const int tid = threadIdx.x;
-#pragma unroll
-  for (int v = 0; v < LR_YPT; ++v)
-    if (tid + v * LR_THREADS < b.rows) ys[tid + v * LR_THREADS] = g.y[v];
-  if (!lr_staged(b.rows, d)) return;
+  if (tid < b.rows) ys[tid] = g.y;
   const int n = b.rows * d, P = lr_spitch(d);
   // element i = row * d + col goes to row * P + col; row and col advance by the
   // elements of one step without a division
@@ -756,11 +749,10 @@ __device__ __forceinline__ float quad_sum(float v) {
   return v;
 }
 
-// r[n] = X[n] . w - y[n] (and rd[n] = X[n] . u when DU).  Staged batches: four
-// threads per row, thread q taking 16-byte groups q, q + 4, ... of the row (w
-// and u zero past d, like the row's padding), and two rows (n and n + 128) per
-// thread at once, sharing the reads of w and u; batches in global memory: one
-// thread per row.  Returns this thread's share of sum_n r[n]^2.
+// r[n] = X[n] . w - y[n] (and rd[n] = X[n] . u when DU): four threads per row,
+// thread q taking 16-byte groups q, q + 4, ... of the row (w and u zero past d,
+// like the row's padding), and two rows (n and n + 128) per thread at once,
+// sharing the reads of w and u.  Returns this thread's share of sum_n r[n]^2.
 template <bool DU>
 __device__ float lr_rows_staged(const float* X, int P, const float* y, const float* w,
                                 const float* u, int rows, int d, float* r, float* rd) {
@@ -811,65 +803,8 @@ __device__ float lr_rows_staged(const float* X, int P, const float* y, const flo
   __syncthreads();
   return sq;
 }
-template <bool DU>
-__device__ float lr_rows_global(const float* X, const float* y, const float* w, const float* u,
-                                int rows, int d, float* r, float* rd) {
-  float sq = 0.0f;
-  for (int n = threadIdx.x; n < rows; n += LR_THREADS) {
-    const float* xr = X + (long)n * d;
-    float s = 0.0f, sd = 0.0f;
-    for (int j = 0; j < d; ++j) {
-      const float x = xr[j];
-      s += x * w[j];
-      if (DU) sd += x * u[j];
-    }
-    const float res = s - y[n];
-    r[n] = res;
-    if (DU) rd[n] = sd;
-    sq += res * res;
-  }
-  __syncthreads();
-  return sq;
-}
-
-// out[j] = sum_n X[n][j] v[n] (and out2 with v2 when DU), j < d; X has row
-// pitch P (LDS or global memory: separate instantiations, so that every access
-// has a known address space; a flat access would wait for the next batch's
-// loads).
-template <bool DU>
-__device__ void lr_cols(const float* X, int P, const float* v, const float* v2, int rows, int d,
-                        float* part, float* part2, float* out, float* out2) {
-  const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-  for (int j0 = 0; j0 < d; j0 += 64) {
-    const int j = j0 + c;
-    float s = 0.0f, s2 = 0.0f;
-    if (j < d) {
-#pragma unroll 4
-      for (int n = q; n < rows; n += LR_RG) {
-        const float x = X[(long)n * P + j];
-        s += x * v[n];
-        if (DU) s2 += x * v2[n];
-      }
-    }
-    part[q * 64 + c] = s;
-    if (DU) part2[q * 64 + c] = s2;
-    __syncthreads();
-    if (threadIdx.x < 64 && j < d) {
-      float a = 0.0f, b = 0.0f;
-#pragma unroll
-      for (int k = 0; k < LR_RG; ++k) {
-        a += part[k * 64 + c];
-        if (DU) b += part2[k * 64 + c];
-      }
-      out[j] = a;
-      if (DU) out2[j] = b;
-    }
-    __syncthreads();
-  }
-}
-
-// The column pass of a staged batch (row pitch P, a multiple of 4, zero past
-// d): each thread takes a 16-byte group of 4 columns and every 32nd row, 16
+// out[j] = sum_n X[n][j] v[n] (and out2 with v2 when DU), j < d, of a staged
+// batch (row pitch P, a multiple of 4, zero past d): each thread takes a 16-byte group of 4 columns and every 32nd row, 16
 // groups (64 columns) per round; the 32 partials of a column are then summed in
 // order, 8 at a time by the 4 lanes of a quad, then across the quad.
 constexpr int LR_CG = 16;                     // column groups per round
@@ -921,15 +856,9 @@ template <bool DU>
 __device__ float lr_pass(const LrBatch& b, int d, const float* stage, const float* ys,
                          const float* w, const float* u, float* r, float* rd, float* part,
                          float* part2, float* g, float* h) {
-  float sq;
-  if (lr_staged(b.rows, d)) {
-    const int P = lr_spitch(d);
-    sq = lr_rows_staged<DU>(stage, P, ys, w, u, b.rows, d, r, rd);
-    lr_cols_staged<DU>(stage, P, r, rd, b.rows, d, part, part2, g, h);
-  } else {
-    sq = lr_rows_global<DU>(b.X, ys, w, u, b.rows, d, r, rd);
-    lr_cols<DU>(b.X, d, r, rd, b.rows, d, part, part2, g, h);
-  }
+  const int P = lr_spitch(d);
+  const float sq = lr_rows_staged<DU>(stage, P, ys, w, u, b.rows, d, r, rd);
+  lr_cols_staged<DU>(stage, P, r, rd, b.rows, d, part, part2, g, h);
   return sq;
 }
 
@@ -944,8 +873,8 @@ __global__ void __launch_bounds__(LR_THREADS) linreg_kernel(LinregArgs a) {
   __shared__ __attribute__((aligned(16))) float th[LR_MAXD], vv[LR_MAXD];
   __shared__ float tb[LR_MAXD], lam[LR_MAXD], eb[LR_MAXD];
   __shared__ float gs[LR_MAXD], hs[LR_MAXD];
-  __shared__ float r[LR_MAXR], rd[LR_MAXR], ys[LR_MAXR];
-  constexpr int NPART = LR_CRG * 4 * LR_CG > LR_RG * 64 ? LR_CRG * 4 * LR_CG : LR_RG * 64;
+  __shared__ float r[LR_DIRECT_ROWS], rd[LR_DIRECT_ROWS], ys[LR_DIRECT_ROWS];
+  constexpr int NPART = LR_CRG * 4 * LR_CG;
   __shared__ __attribute__((aligned(16))) float part[NPART], part2[NPART];
   __shared__ float red[LR_THREADS / 64];
   const int tid = threadIdx.x, d = a.d, T = a.T;
@@ -1034,6 +963,8 @@ constexpr int LRR_RPT = 8;                          // rows per thread
 constexpr int LRR_SLOTS = LR_THREADS / 16;          // row slots (32)
 constexpr int LRR_MAXROWS = LRR_SLOTS * LRR_RPT;    // 256
 constexpr int LRR_MAXD = 64;
+constexpr int LRR_MAXT = 6;
+static_assert((LRR_MAXT + 1) * LRR_MAXD <= LR_CKPT, "checkpoints in LDS");
 
 struct LrrRegs {
   float4 x[LRR_RPT];  // group c of rows q + 32 u
@@ -1070,12 +1001,9 @@ __device__ __forceinline__ float row16_sum(float v) {
   return quad_sum(v);
 }
 
-// CKL: the checkpoints fit in LDS ((T + 1) d <= 4096).  A compile-time choice,
-// since a runtime one merges the two checkpoint reads into one flat load, which
-// waits for every global load in flight, the next batch's included.
-template <bool CKL>
+// The checkpoints stay in LDS: the path is taken for at most LRR_MAXT steps.
 __global__ void __launch_bounds__(LR_THREADS) linreg_reg_kernel(LinregArgs a) {
-  __shared__ float ck[CKL ? LR_CKPT : 1];
+  __shared__ float ck[LR_CKPT];
   __shared__ __attribute__((aligned(16))) float th[LRR_MAXD], vv[LRR_MAXD];
   __shared__ __attribute__((aligned(16))) float part[LRR_SLOTS * LRR_MAXD];
   __shared__ __attribute__((aligned(16))) float part2[LRR_SLOTS * LRR_MAXD];
@@ -1103,8 +1031,7 @@ __global__ void __launch_bounds__(LR_THREADS) linreg_reg_kernel(LinregArgs a) {
     th[tid] = in ? th0 : 0.0f;   // zero past d, like vv: the groups past d add nothing
     vv[tid] = 0.0f;
     if (in) {
-      if constexpr (CKL) ck[tid] = th0;
-      else a.ckpt[tid] = th0;
+      ck[tid] = th0;
     }
   }
   __syncthreads();
@@ -1157,8 +1084,7 @@ __global__ void __launch_bounds__(LR_THREADS) linreg_reg_kernel(LinregArgs a) {
     {
       const int i = 2 * T - k;
       if (k >= T && i >= 1 && (tid & 3) == 0 && tid < 4 * d) {
-        if constexpr (CKL) thn = ck[(i - 1) * d + (tid >> 2)];
-        else thn = a.ckpt[(long)(i - 1) * d + (tid >> 2)];
+        thn = ck[(i - 1) * d + (tid >> 2)];
       }
     }
     reinterpret_cast<float4*>(part)[q * 16 + c] = ga;
@@ -1186,8 +1112,7 @@ __global__ void __launch_bounds__(LR_THREADS) linreg_reg_kernel(LinregArgs a) {
           const float t = thr - lamr * inv * g;
           thr = t;
           th[j] = t;
-          if constexpr (CKL) ck[(k + 1) * d + j] = t;
-          else a.ckpt[(long)(k + 1) * d + j] = t;
+          ck[(k + 1) * d + j] = t;
         } else {
           // validation: bar theta_T = dV/dtheta_T; reverse step i = 2T - k:
           // bar eta += -exp(eta) g_i bar theta_{i+1}; bar theta_i = bar theta_{i+1} + H v
@@ -1461,18 +1386,25 @@ hipError_t linreg_meta_grad(const float* theta0, const float* eta, const float* 
   a.d_eta = d_eta;
   a.val_loss = val_loss;
   a.ckpt = scratch;
-  // batches that fit one register set per thread: the register-resident kernel;
-  // else batches staged in LDS (16-byte or 4-byte loads) or read from global memory
-  if (a.vec && d <= LRR_MAXD && rows <= LRR_MAXROWS && vrows <= LRR_MAXROWS) {
-    if ((T + 1) * d <= LR_CKPT)
-      hipLaunchKernelGGL(linreg_reg_kernel<true>, dim3(1), dim3(LR_THREADS), 0, s, a);
+  // One workgroup pays about 1.6 us a phase (2 T + 1 phases) to walk a batch in its
+  // registers, the normal equations 0.5 us after some 18 us for the matrices and
+  // three launches: 64 features, 256 rows: T = 4 17 against 25 us, T = 8 29 against
+  // 23 (64 rows), T = 64 206 against 71.
+  if (a.vec && d <= LRR_MAXD && rows <= LRR_MAXROWS && vrows <= LRR_MAXROWS && T <= LRR_MAXT) {
+    hipLaunchKernelGGL(linreg_reg_kernel, dim3(1), dim3(LR_THREADS), 0, s, a);
+    return hipGetLastError();
+  }
+  // Batches much smaller than their d x d matrices: 256 features, 64 rows, T = 4: 52
+  // against 69 us (200 features, 50 rows: 51 against 41; 256 rows: 324 against 70).
+  if (d > LR_DIRECT_D && rows <= LR_DIRECT_ROWS && vrows <= LR_DIRECT_ROWS) {
+    if (a.vec)
+      hipLaunchKernelGGL(linreg_kernel<true>, dim3(1), dim3(LR_THREADS), 0, s, a);
     else
-      hipLaunchKernelGGL(linreg_reg_kernel<false>, dim3(1), dim3(LR_THREADS), 0, s, a);
-  } else if (a.vec)
-    hipLaunchKernelGGL(linreg_kernel<true>, dim3(1), dim3(LR_THREADS), 0, s, a);
-  else
-    hipLaunchKernelGGL(linreg_kernel<false>, dim3(1), dim3(LR_THREADS), 0, s, a);
-  return hipGetLastError();
+      hipLaunchKernelGGL(linreg_kernel<false>, dim3(1), dim3(LR_THREADS), 0, s, a);
+    return hipGetLastError();
+  }
+  return linreg_gram_meta_grad(theta0, eta, xs, ys, T, rows, d, vx, vy, vrows, d_eta, val_loss,
+                               scratch, s);
 }
 
 template hipError_t convert_matrices<bf16_t>(const ConvJobs<bf16_t>&, int, int, int, int, int, hipStream_t, int, long, long, long);

@@ -303,13 +303,19 @@ hipError_t adam_reduce(const float* partial, const int* block_offsets, int n_lay
                        float* d_eta, hipStream_t s);
 
 // Linear regression, SGD with per-parameter log learning rates, squared loss:
-// the whole meta-gradient in one workgroup.  xs, ys: host arrays of T device
-// pointers; scratch: (T + 1) * d floats of device memory.
+// the whole meta-gradient.  xs, ys: host arrays of T device pointers; scratch:
+// linreg_scratch_floats(T, d) floats of device memory.
 hipError_t linreg_meta_grad(const float* theta0, const float* eta, const float* const* xs,
                             const float* const* ys, int T, int rows, int d, const float* vx,
                             const float* vy, int vrows, float* d_eta, float* val_loss,
                             float* scratch, hipStream_t s);
 bool linreg_fits(int T, int rows, int vrows, int d);
+long linreg_scratch_floats(int T, int d);
+// Its form through the normal equations of the batches (linreg.hip).
+hipError_t linreg_gram_meta_grad(const float* theta0, const float* eta, const float* const* xs,
+                                 const float* const* ys, int T, int rows, int d, const float* vx,
+                                 const float* vy, int vrows, float* d_eta, float* val_loss,
+                                 float* scratch, hipStream_t s);
 
 // Fill / copy float arrays with kernels (no memset or memcpy nodes, so the
 // calls stay safe inside captured HIP graphs).
