@@ -87,14 +87,14 @@ struct mfmg_problem {
            d.precision == MFMG_PREC_FP32 && linreg_fits(T, d.rows, d.val_rows, w[0]);
   }
   int maxR() const { return d.rows > d.val_rows ? d.rows : d.val_rows; }
-  // Length of a contraction over n elements of operand rows: with bf16 operands
-  // n rounded up to their 16-byte chunks, so that every product takes the
+  // Length of a contraction over n elements of operand rows: n rounded up to
+  // their 16-byte chunks, so that every product takes the
   // direct-to-LDS path whatever its widths and rows are.  The rows' padding is
   // zero: the producers of activations and gradients write it with each row, and
   // zero_pads clears that of the weights' copies once per call.  (A 781-1000-515-37
   // ReLU network, 250 rows, T = 4: 1.92 ms with the ragged products on the
   // register-staged kernel's single-element loads, 0.65 ms padded.)
-  int kx(int n) const { return bf16() ? (int)ld(n) : n; }
+  int kx(int n) const { return (int)ld(n); }
 };
 
 namespace {
@@ -527,11 +527,11 @@ struct Eng {
 
 // The padding of every weight copy's rows (columns nout .. ld - 1 of W, nin .. ld
 // - 1 of W^T) set to zero in every operand set of a call; nothing else writes
-// there, so it stays zero for the whole call.  bf16 operands only (see kx).
+// there, so it stays zero for the whole call (see kx).
 template <typename T>
 mfmg_status zero_pads(const mfmg_problem* p, const std::vector<const OperandSet<T>*>& sets,
                       hipStream_t s) {
-  if (!p->bf16()) return MFMG_OK;
+  constexpr int HW = sizeof(T) / 2;   // the fill counts 2-byte units
   ZeroColJobs J;
   J.n = 0;
   auto add = [&](T* q, int rows, int cols) -> mfmg_status {
@@ -542,8 +542,8 @@ mfmg_status zero_pads(const mfmg_problem* p, const std::vector<const OperandSet<
     }
     J.p[J.n] = reinterpret_cast<uint16_t*>(q);
     J.rows[J.n] = rows;
-    J.ld[J.n] = J.c1[J.n] = (int)p->ld(cols);
-    J.c0[J.n] = cols;
+    J.ld[J.n] = J.c1[J.n] = (int)p->ld(cols) * HW;
+    J.c0[J.n] = cols * HW;
     ++J.n;
     return MFMG_OK;
   };

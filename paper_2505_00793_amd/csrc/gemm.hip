@@ -59,6 +59,14 @@ __device__ __forceinline__ float sum8(const u32x4& u) {
   }
   return ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
 }
+// The elements of type T in 16 bytes, summed in float32.
+template <typename T>
+__device__ __forceinline__ float sum16(const u32x4& u) {
+  if constexpr (sizeof(T) == 2) return sum8(u);
+  else
+    return (__uint_as_float(u[0]) + __uint_as_float(u[1])) +
+           (__uint_as_float(u[2]) + __uint_as_float(u[3]));
+}
 
 __device__ __forceinline__ void mma(f32x4& acc, const bf16x8& a, const bf16x8& b) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
@@ -991,19 +999,32 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-template <int FLAGS, int BM, int BN, int BK, int NST, int NPASS>
+// Direct-to-LDS pipeline shape.  The k depth is 64 bf16 or 32 float32 elements
+// (128-byte rows): each 1 KB
+// load then covers 8 whole 128-byte lines, where 64-byte rows make it touch 16
+// half lines and halve the load unit's throughput.  Stages: as many 32 KB
+// (two tiles), 48 KB (three) or 64 KB (four) stages as fit in 144 KB.
+template <typename T, int FLAGS>
+struct DmaShape {
+  static constexpr int NOPS = ((FLAGS & (G_C1 | G_BD)) ? 1 : 0) + ((FLAGS & G_AD) ? 1 : 0) +
+                              ((FLAGS & (G_C1 | G_AD)) ? 1 : 0) + ((FLAGS & G_BD) ? 1 : 0);
+  static constexpr int BK = 128 / (int)sizeof(T);
+  static constexpr int NST = NOPS <= 2 ? 4 : NOPS == 3 ? 3 : 2;
+};
+
+template <typename T, int FLAGS, int BM, int BN, int BK, int NST, int NPASS>
 struct DmaSmem {
   static constexpr bool LA = (FLAGS & (G_C1 | G_BD)) != 0;  // tiles loaded
   static constexpr bool LAD = (FLAGS & G_AD) != 0;
   static constexpr bool LB = (FLAGS & (G_C1 | G_AD)) != 0;
   static constexpr bool LBD = (FLAGS & G_BD) != 0;
-  static constexpr int ROWB = BK * 2;                         // bytes per tile row
+  static constexpr int ROWB = BK * (int)sizeof(T);            // bytes per tile row
   static constexpr int OFF_AD = (LA ? BM : 0) * ROWB;
   static constexpr int OFF_B = OFF_AD + (LAD ? BM : 0) * ROWB;
   static constexpr int OFF_BD = OFF_B + (LB ? BN : 0) * ROWB;
   static constexpr int STAGE_BYTES = OFF_BD + (LBD ? BN : 0) * ROWB;
   static constexpr int NOPS = (LA ? 1 : 0) + (LAD ? 1 : 0) + (LB ? 1 : 0) + (LBD ? 1 : 0);
-  static constexpr int CPR = BK / 8;
+  static constexpr int CPR = ROWB / 16;
   static constexpr int LPW = STAGE_BYTES / 1024 / 4;         // load instructions per wave
   static constexpr int PIPE_BYTES = NST * STAGE_BYTES;
   static constexpr int EPI_BYTES = EpiSmem<FLAGS, BM, BN, NPASS>::BYTES;
@@ -1011,8 +1032,9 @@ struct DmaSmem {
 };
 
 // Per-lane state for one operand tile: which rows this lane fetches.
-template <int ROWS, int CPR>
+template <typename T, int ROWS, int CPR>
 struct DmaTile {
+  static constexpr int VE = Elem<T>::VE, ES = (int)sizeof(T);
   static constexpr int RPB = 64 / CPR;         // tile rows per 1 KB load
   static constexpr int BPW = ROWS / RPB / 4;   // loads per wave per k step
   static_assert(BPW >= 1 && ROWS % (4 * RPB) == 0, "tile rows");
@@ -1021,10 +1043,9 @@ struct DmaTile {
   int kq;                  // element offset of the lane's chunk within a k step
 
   // w: index 0..3 of this wave among the four that load the tile
-  __device__ __forceinline__ void init(const bf16_t* base, int rows, int ld, int K, int row0,
-                                       int w) {
-    const unsigned bytes = rows > 0 ? (unsigned)(((long)(rows - 1) * ld + K) * 2) : 0u;
-    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)bytes, 0x00020000);
+  __device__ __forceinline__ void init(const T* base, int rows, int ld, int K, int row0, int w) {
+    const unsigned bytes = rows > 0 ? (unsigned)(((long)(rows - 1) * ld + K) * ES) : 0u;
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, (int)bytes, 0x00020000);
     const int lane = threadIdx.x & 63;
     const int p = lane % CPR;
 #pragma unroll
@@ -1032,8 +1053,8 @@ struct DmaTile {
       const int r = (c * 4 + w) * RPB + lane / CPR;
       const int q = p ^ chunk_swizzle<CPR>(r);
       const int gr = row0 + r;
-      row_off[c] = gr < rows ? (unsigned)((long)gr * ld + q * 8) * 2u : 0x80000000u;
-      kq = q * 8;   // the same for every c: the swizzle reads row bits that c does not change
+      row_off[c] = gr < rows ? (unsigned)((long)gr * ld + q * VE) * ES : 0x80000000u;
+      kq = q * VE;   // the same for every c: the swizzle reads row bits that c does not change
     }
   }
   // Issue the loads of k step k0 into the tile at dst (LDS).
@@ -1041,7 +1062,7 @@ struct DmaTile {
     const bool kin = k0 + kq < K;
 #pragma unroll
     for (int c = 0; c < BPW; ++c) {
-      const unsigned off = (kin && row_off[c] != 0x80000000u) ? row_off[c] + (unsigned)k0 * 2u
+      const unsigned off = (kin && row_off[c] != 0x80000000u) ? row_off[c] + (unsigned)k0 * ES
                                                              : 0x80000000u;
       char* d = dst + (c * 4 + w) * RPB * (CPR * 16);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)d, 16, off, 0, 0, 0);
@@ -1058,10 +1079,12 @@ struct DmaTile {
 // that keeps its matrix core busy while the other waits on the load unit.  The
 // eight waves meet at one barrier per k step and all of them walk the epilogue.
 // ------------------------------------------------------------------------------------
-template <int FLAGS, int BM, int BN, int BK, int NST, class Epi>
-__device__ __forceinline__ void gemm_ws_tile(const GemmOperands<bf16_t>& op, const Epi& epi,
-                                             int pid, int bz, char* smem) {
-  typedef DmaSmem<FLAGS, BM, BN, BK, NST, 1> SM;
+template <typename T, int FLAGS, int BM, int BN, int NST, class Epi>
+__device__ __forceinline__ void gemm_ws_tile(const GemmOperands<T>& op, const Epi& epi, int pid,
+                                             int bz, char* smem) {
+  constexpr int BK = DmaShape<T, FLAGS>::BK;
+  typedef DmaSmem<T, FLAGS, BM, BN, BK, NST, 1> SM;
+  typedef typename Frag<T>::type frag_t;
   constexpr bool HC1 = (FLAGS & G_C1) != 0;
   constexpr bool HAD = (FLAGS & G_AD) != 0;
   constexpr bool HBD = (FLAGS & G_BD) != 0;
@@ -1088,8 +1111,8 @@ __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<bf16_t>& op, con
   // staging buffer and one when the staged tile is complete.
   if (wave >= 4) {
     const int pw = wave - 4;
-    DmaTile<BM, CPR> tA, tAd;
-    DmaTile<BN, CPR> tB, tBd;
+    DmaTile<T, BM, CPR> tA, tAd;
+    DmaTile<T, BN, CPR> tB, tBd;
     if constexpr (SM::LA) tA.init(op.A + bz * op.sA, op.M, op.lda, K, m0, pw);
     if constexpr (SM::LAD) tAd.init(op.Ad + bz * op.sA, op.M, op.lda, K, m0, pw);
     if constexpr (SM::LB) tB.init(op.B + bz * op.sB, op.N, op.ldb, K, n0, pw);
@@ -1150,8 +1173,8 @@ __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<bf16_t>& op, con
             if constexpr (SM::LB) u = lds_read16(st + SM::OFF_B + off);
             if constexpr (SM::LBD) ud = lds_read16(st + SM::OFF_BD + off);
             lds_read_wait();
-            if constexpr (SM::LB) bsum += sum8(u);
-            if constexpr (SM::LBD) bdsum += sum8(ud);
+            if constexpr (SM::LB) bsum += sum16<T>(u);
+            if constexpr (SM::LBD) bdsum += sum16<T>(ud);
           }
         }
       }
@@ -1196,20 +1219,20 @@ __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<bf16_t>& op, con
       constexpr int NF = SM::NOPS <= 2 ? NCH : 1;
 #pragma unroll
       for (int c0 = 0; c0 < NCH; c0 += NF) {
-        bf16x8 a[NF][TM], ad[NF][TM], b[NF][TN], bd[NF][TN];
+        frag_t a[NF][TM], ad[NF][TM], b[NF][TN], bd[NF][TN];
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
 #pragma unroll
           for (int i = 0; i < TM; ++i) {
             const int r0 = (wm * WTM + i * 16) * ROWB + foff[c0 + f];
-            if constexpr (SM::LA) a[f][i] = *reinterpret_cast<const bf16x8*>(As + r0);
-            if constexpr (HAD) ad[f][i] = *reinterpret_cast<const bf16x8*>(Ads + r0);
+            if constexpr (SM::LA) a[f][i] = *reinterpret_cast<const frag_t*>(As + r0);
+            if constexpr (HAD) ad[f][i] = *reinterpret_cast<const frag_t*>(Ads + r0);
           }
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
             const int r0 = (wn * WTN + j * 16) * ROWB + foff[c0 + f];
-            if constexpr (SM::LB) b[f][j] = *reinterpret_cast<const bf16x8*>(Bs + r0);
-            if constexpr (HBD) bd[f][j] = *reinterpret_cast<const bf16x8*>(Bds + r0);
+            if constexpr (SM::LB) b[f][j] = *reinterpret_cast<const frag_t*>(Bs + r0);
+            if constexpr (HBD) bd[f][j] = *reinterpret_cast<const frag_t*>(Bds + r0);
           }
         }
 #pragma unroll
@@ -1233,10 +1256,11 @@ __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<bf16_t>& op, con
   walk_tile<FLAGS, BN, BM, 512>(S1, S2, m0, n0, bz, epi);
 }
 
-template <int FLAGS, int BM, int BN, int BK, int NST, class Epi>
-__global__ void __launch_bounds__(512) gemm_nt_ws(GemmOperands<bf16_t> op, Epi epi) {
-  __shared__ __attribute__((aligned(1024))) char smem[DmaSmem<FLAGS, BM, BN, BK, NST, 1>::BYTES];
-  gemm_ws_tile<FLAGS, BM, BN, BK, NST, Epi>(op, epi, (int)blockIdx.x, (int)blockIdx.y, smem);
+template <typename T, int FLAGS, int BM, int BN, int NST, class Epi>
+__global__ void __launch_bounds__(512) gemm_nt_ws(GemmOperands<T> op, Epi epi) {
+  __shared__ __attribute__((aligned(1024))) char
+      smem[DmaSmem<T, FLAGS, BM, BN, DmaShape<T, FLAGS>::BK, NST, 1>::BYTES];
+  gemm_ws_tile<T, FLAGS, BM, BN, NST, Epi>(op, epi, (int)blockIdx.x, (int)blockIdx.y, smem);
 }
 
 // Two independent products in one launch, for products too small to fill the
@@ -1249,8 +1273,8 @@ template <int F1, int BM1, int BN1, int NST1, class E1, int F2, int BM2, int BN2
 __global__ void __launch_bounds__(512) gemm_pair_ws(GemmOperands<bf16_t> op1, E1 epi1, int t1,
                                                     int g1, GemmOperands<bf16_t> op2, E2 epi2,
                                                     int t2, int g2) {
-  constexpr int B1 = DmaSmem<F1, BM1, BN1, 64, NST1, 1>::BYTES;
-  constexpr int B2 = DmaSmem<F2, BM2, BN2, 64, NST2, 1>::BYTES;
+  constexpr int B1 = DmaSmem<bf16_t, F1, BM1, BN1, 64, NST1, 1>::BYTES;
+  constexpr int B2 = DmaSmem<bf16_t, F2, BM2, BN2, 64, NST2, 1>::BYTES;
   __shared__ __attribute__((aligned(1024))) char smem[B1 > B2 ? B1 : B2];
   const int b = (int)blockIdx.x;
   const int period = g1 + g2;
@@ -1267,9 +1291,9 @@ __global__ void __launch_bounds__(512) gemm_pair_ws(GemmOperands<bf16_t> op1, E1
     j = which == 0 ? cyc * g1 + r : cyc * g2 + (r - rest1);
   }
   if (which == 0)
-    gemm_ws_tile<F1, BM1, BN1, 64, NST1, E1>(op1, epi1, j, 0, smem);
+    gemm_ws_tile<bf16_t, F1, BM1, BN1, NST1, E1>(op1, epi1, j, 0, smem);
   else
-    gemm_ws_tile<F2, BM2, BN2, 64, NST2, E2>(op2, epi2, j, 0, smem);
+    gemm_ws_tile<bf16_t, F2, BM2, BN2, NST2, E2>(op2, epi2, j, 0, smem);
 }
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -1298,39 +1322,29 @@ struct KDepth<G_BD, ParamOp<T>> {
   static constexpr int value = 32;
 };
 
-// Direct-to-LDS pipeline shape.  The k depth is 64 (128-byte rows): each 1 KB
-// load then covers 8 whole 128-byte lines, where 64-byte rows make it touch 16
-// half lines and halve the load unit's throughput.  Stages: as many 32 KB
-// (two tiles), 48 KB (three) or 64 KB (four) stages as fit in 144 KB.
-template <int FLAGS>
-struct DmaShape {
-  static constexpr int NOPS = ((FLAGS & (G_C1 | G_BD)) ? 1 : 0) + ((FLAGS & G_AD) ? 1 : 0) +
-                              ((FLAGS & (G_C1 | G_AD)) ? 1 : 0) + ((FLAGS & G_BD) ? 1 : 0);
-  static constexpr int BK = 64;
-  static constexpr int NST = NOPS <= 2 ? 4 : NOPS == 3 ? 3 : 2;
-};
-
 // Pipeline depth of the small tiles (64 x 64, 64 x 32), whose products are
 // bound by load latency rather than by delivery: as many stages as fit in an
 // LDS budget per workgroup (144 KB with one workgroup per compute unit, 72 KB
 // with two), 2 to 8.
-template <int FLAGS, int BM, int BN, int BUDGET>
+template <typename T, int FLAGS, int BM, int BN, int BUDGET>
 struct DmaDepth {
-  static constexpr int STAGE = DmaSmem<FLAGS, BM, BN, 64, 2, 1>::STAGE_BYTES;
+  static constexpr int STAGE =
+      DmaSmem<T, FLAGS, BM, BN, DmaShape<T, FLAGS>::BK, 2, 1>::STAGE_BYTES;
   static constexpr int N0 = BUDGET / STAGE;
-  static constexpr int NST = BM > 64 ? DmaShape<FLAGS>::NST : N0 < 2 ? 2 : N0 > 8 ? 8 : N0;
+  static constexpr int NST = BM > 64 ? DmaShape<T, FLAGS>::NST : N0 < 2 ? 2 : N0 > 8 ? 8 : N0;
 };
 
 template <typename T>
 bool dma_operand_ok(const T* p, int rows, int ld, int K, long stride) {
   if (!p) return true;
-  if ((reinterpret_cast<uintptr_t>(p) & 15) || (ld & 7) || (stride & 7)) return false;
+  constexpr int VE = 16 / (int)sizeof(T);
+  if ((reinterpret_cast<uintptr_t>(p) & 15) || ld % VE || stride % VE) return false;
   return rows <= 0 || ((long)(rows - 1) * ld + K) * (long)sizeof(T) < (1L << 31);
 }
 
 template <typename T>
 bool dma_ok(const GemmOperands<T>& op) {
-  if (sizeof(T) != 2 || (op.K & 7)) return false;
+  if (op.K <= 0 || op.K % (16 / (int)sizeof(T))) return false;
   return dma_operand_ok(op.A, op.M, op.lda, op.K, op.sA) &&
          dma_operand_ok(op.Ad, op.M, op.lda, op.K, op.sA) &&
          dma_operand_ok(op.B, op.N, op.ldb, op.K, op.sB) &&
@@ -1340,23 +1354,22 @@ bool dma_ok(const GemmOperands<T>& op) {
 template <typename T, int FLAGS, int BM, int BN, class Epi>
 hipError_t launch(const GemmOperands<T>& op, const Epi& epi, hipStream_t s) {
   const int tiles = cdiv(op.M, BM) * cdiv(op.N, BN);
-  if constexpr (sizeof(T) == 2) {
-    typedef DmaShape<FLAGS> DS;
+  if constexpr (BN >= 32) {
     if (dma_ok(op)) {
       if constexpr (BM == 64) {
         if (tiles * op.batch <= 256) {   // one workgroup per compute unit: a deeper ring
-          constexpr int NST = DmaDepth<FLAGS, BM, BN, 147456>::NST;
-          hipLaunchKernelGGL((gemm_nt_ws<FLAGS, BM, BN, DS::BK, NST, Epi>), dim3(tiles, op.batch),
+          constexpr int NST = DmaDepth<T, FLAGS, BM, BN, 147456>::NST;
+          hipLaunchKernelGGL((gemm_nt_ws<T, FLAGS, BM, BN, NST, Epi>), dim3(tiles, op.batch),
                              dim3(512), 0, s, op, epi);
           return hipGetLastError();
         }
       }
-      hipLaunchKernelGGL((gemm_nt_ws<FLAGS, BM, BN, DS::BK, DS::NST, Epi>), dim3(tiles, op.batch),
-                         dim3(512), 0, s, op, epi);
+      hipLaunchKernelGGL((gemm_nt_ws<T, FLAGS, BM, BN, DmaShape<T, FLAGS>::NST, Epi>),
+                         dim3(tiles, op.batch), dim3(512), 0, s, op, epi);
       return hipGetLastError();
     }
   }
-  if constexpr (BN >= 64 || BN == 16) {
+  if constexpr (BM == 64 && (BN == 64 || BN == 16)) {
     constexpr int BK = BN == 16 ? 64 : KDepth<FLAGS, Epi>::value;
     if (op.K % Elem<T>::VE == 0)
       hipLaunchKernelGGL((gemm_nt<T, FLAGS, BM, BN, BK, Epi, true>), dim3(tiles, op.batch),
@@ -1489,7 +1502,7 @@ hipError_t launch_splitk(const GemmOperands<T>& op, const Epi& epi, int S, hipSt
   e.C = op.ws; e.Cd = op.ws + S * MN; e.ldc = op.N; e.sC = MN; e.scale = 1.0f;
   e.M = op.M; e.N = op.N; e.dual = HC2 ? 1 : 0;
   hipError_t r;
-  if constexpr (sizeof(T) == 2)
+  if (sizeof(T) == 2 && dma_ok(p))
     r = launch<T, FLAGS, 128, 128>(p, StoreOp{e, op.M, op.N}, s);
   else
     r = launch<T, FLAGS, 64, 64>(p, StoreOp{e, op.M, op.N}, s);
@@ -1526,7 +1539,7 @@ hipError_t launch_sized(const GemmOperands<T>& op, const Epi& epi, hipStream_t s
         return launch_splitk<T, FLAGS>(op, epi, S, s);
     }
   }
-  if constexpr (sizeof(T) == 2) {
+  if (dma_ok(op)) {
     // 128 x 128 tiles once they alone fill most of the 256 compute units, else
     // 128 x 64 on the direct-to-LDS path (each compute unit then loads 128 + 64
     // rows per k step for 8192 outputs against 2 x 128 for two 64 x 64 tiles),
@@ -1535,9 +1548,9 @@ hipError_t launch_sized(const GemmOperands<T>& op, const Epi& epi, hipStream_t s
     // workgroups instead of 128).
     if (cdiv(op.M, 128) * cdiv(op.N, 128) * op.batch >= 192)
       return launch<T, FLAGS, 128, 128>(op, epi, s);
-    if (cdiv(op.M, 128) * cdiv(op.N, 64) * op.batch >= 192 && dma_ok(op))
+    if (cdiv(op.M, 128) * cdiv(op.N, 64) * op.batch >= 192)
       return launch<T, FLAGS, 128, 64>(op, epi, s);
-    if (cdiv(op.M, 64) * cdiv(op.N, 64) * op.batch < 192 && dma_ok(op))
+    if (cdiv(op.M, 64) * cdiv(op.N, 64) * op.batch < 192)
       return launch<T, FLAGS, 64, 32>(op, epi, s);
   }
   return launch<T, FLAGS, 64, 64>(op, epi, s);
@@ -1580,8 +1593,8 @@ hipError_t launch_pair(const GemmOperands<bf16_t>& o1, const E1& e1,
   if (t2 >= t1) g2 = 8 * max(1, (t2 + t1 / 2) / max(t1, 1));
   else g1 = 8 * max(1, (t1 + t2 / 2) / max(t2, 1));
   // at most two workgroups per compute unit: 72 KB rings
-  hipLaunchKernelGGL((gemm_pair_ws<F1, BM1, BN1, DmaDepth<F1, BM1, BN1, 73728>::NST, E1, F2, BM2,
-                                   BN2, DmaDepth<F2, BM2, BN2, 73728>::NST, E2>),
+  hipLaunchKernelGGL((gemm_pair_ws<F1, BM1, BN1, DmaDepth<bf16_t, F1, BM1, BN1, 73728>::NST, E1, F2, BM2,
+                                   BN2, DmaDepth<bf16_t, F2, BM2, BN2, 73728>::NST, E2>),
                      dim3(t1 + t2), dim3(512), 0, s, o1, e1, t1, g1, o2, e2, t2, g2);
   return hipGetLastError();
 }

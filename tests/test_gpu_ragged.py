@@ -1,5 +1,6 @@
-"""bf16 products whose contractions are padded to whole 16-byte chunks: widths and rows of every
-residue modulo 8, in a workspace full of NaN, against the oracle's bf16 emulation."""
+"""Products whose contractions are padded to whole 16-byte chunks: widths and rows of every residue
+modulo 8 (bf16) and 4 (float32), on every tile size of the direct-to-LDS kernel, in a workspace full
+of NaN, against the oracle."""
 import numpy as np
 import pytest
 
@@ -13,10 +14,18 @@ CASES = [  # widths, rows, val_rows, optimiser family
     ((65, 130, 67, 3), 60, 43, W.C5), ((61, 35, 44, 5), 121, 129, W.C5),
     ((9, 1, 7, 2), 3, 1, W.C5), ((70, 131, 6), 37, 64, W.C3), ((64, 128, 136), 65, 8, W.C5),
     ((66, 257), 127, 130, W.C5),
+    # float32: 64 x 16 and 64 x 32 tiles, split-K, 64 x 64, 128 x 64 and 128 x 128 tiles
+    ((61, 35, 44, 5), 121, 129, W.C2), ((530, 33, 130, 18), 67, 258, W.C2),
+    ((9, 1, 7, 2), 3, 1, W.C2.with_(optimizer=W.OPT_ADAM, meta=W.META_LOGLR_PER_LAYER_WD)),
+    ((1030, 1537), 197, 130, W.C2), ((1541, 2050), 133, 70, W.C2),
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c[0])))
+def _id(case):
+    return "-".join(map(str, case[0])) + ("-f32" if case[3].precision == W.PREC_FP32 else "")
+
+
+@pytest.mark.parametrize("case", CASES, ids=_id)
 def test_padded_contractions(case):
     import torch
     if not torch.cuda.is_available():
@@ -32,6 +41,6 @@ def test_padded_contractions(case):
     d = torch.empty(W.n_eta(cfg), device="cuda")
     P.mfmg_meta_grad(dev["theta0"], dev["opt_state0"], dev["eta"], dev["xs"], dev["ys"], dev["vx"],
                      dev["vy"], d, ws=ws)
-    ref, _ = oracle.meta_grad(cfg, inp, bf16=True)
+    ref, _ = oracle.meta_grad(cfg, inp, bf16=cfg.precision == W.PREC_BF16)
     errs = group_errors(cfg, d.cpu().numpy().astype(np.float64), ref)
     assert max(errs) <= tol_of(cfg), errs
