@@ -10,12 +10,10 @@ typedef uint16_t bf16_t;  // bfloat16 storage
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// float -> bfloat16, round to nearest even (add 0x7fff plus the lsb of the kept
-// half, then truncate).  Inputs are finite.
+// float -> bfloat16, round to nearest even, by the hardware's conversion (the
+// compiler pairs two of them into one v_cvt_pk_bf16_f32).
 __device__ __forceinline__ bf16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
+  return __builtin_bit_cast(bf16_t, (__bf16)f);
 }
 __device__ __forceinline__ float bf2f(bf16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
