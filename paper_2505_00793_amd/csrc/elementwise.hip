@@ -46,10 +46,17 @@ __global__ void __launch_bounds__(256) convert_kernel(ConvJobs<T> J, int batch, 
   T* dstT = P.dstT;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int cols_w = J.zpad ? ldd : cols, rows_w = J.zpad ? lddT : rows;   // written
-  for (int i = ty; i < 64; i += 4) {
-    const int r = r0 + i, c = c0 + tx;
-    float v = 0.0f;
-    if (r < rows && c < cols) v = src[(long)r * lds + c];
+  // a thread's sixteen rows requested together, from indices clamped into the
+  // matrix (256 x 781: 11.6 us a launch with each load behind its own branch)
+  const int c = c0 + tx;
+  float x[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u)
+    x[u] = src[(long)min(r0 + ty + 4 * u, rows - 1) * lds + min(c, cols - 1)];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int i = ty + 4 * u, r = r0 + i;
+    const float v = r < rows && c < cols ? x[u] : 0.0f;
     if (dst && r < rows && c < cols_w) dst[(long)r * ldd + c] = Elem<T>::from_float(v);
     tile[i][tx] = v;
   }
@@ -265,6 +272,82 @@ __global__ void __launch_bounds__(256) bias_kernel(const T* __restrict__ dZT,
 // (d^2 L / d alpha_n d theta) v of Section 3 (eq. vmp_to_mvp) for loss weights.
 // ------------------------------------------------------------------------------------
 template <typename T>
+__device__ __forceinline__ void loss_row_out(const LossArgs<T>& a, int row, float w, float loss,
+                                             float ldot) {
+  if (a.loss_rows) a.loss_rows[row] = loss;
+  if (a.mvp_rows) a.mvp_rows[row] = ldot * a.inv_n;
+  if (a.deta_rows) a.deta_rows[row] = w * (1.0f - w) * ldot * a.inv_n;
+}
+
+// Squared error after the M-step map y_i = i (2 + sin y_{i-1})^cos y_{i-1},
+// mean over the C outputs, for one output z (tangent zd, target t): dL/dz to d,
+// its tangent to dd, and the loss and its tangent added.  The map's value y_M
+// and its first and second derivatives in z are carried through the M steps in
+// registers (with h = d/dy ln f_i = cos^2 y / (2 + sin y) - sin y ln(2 + sin y):
+// f_i' = f_i h, f_i'' = f_i (h^2 + h')), so no step is stored.
+template <typename T>
+__device__ __forceinline__ void map_loss_elem(const LossArgs<T>& a, float z, float zd, float t,
+                                              float scale, float& d, float& dd, float& loss,
+                                              float& ldot) {
+  const float invC = 1.0f / (float)a.C;
+  float g = z, g1 = 1.0f, g2 = 0.0f;
+  for (int i = 1; i <= a.map_M; ++i) {
+    float sn, cs;
+    sincosf(g, &sn, &cs);
+    const float u = 2.0f + sn, lu = logf(u), iu = 1.0f / u;
+    const float f = (float)i * expf(cs * lu);
+    const float h = cs * cs * iu - sn * lu;
+    const float hp = -cs * lu - 3.0f * sn * cs * iu - cs * cs * cs * iu * iu;
+    const float f1 = f * h, f2 = f * (h * h + hp);
+    g2 = f2 * g1 * g1 + f1 * g2;
+    g1 = f1 * g1;
+    g = f;
+  }
+  const float r = g - t;
+  loss += r * r * invC;
+  dd = 0.0f;
+  if (a.dual) {
+    ldot += 2.0f * invC * r * g1 * zd;
+    dd = 2.0f * scale * invC * zd * (g1 * g1 + r * g2);
+  }
+  d = 2.0f * scale * invC * r * g1;
+}
+
+// The map loss (a.loss == 2) of one row on 256 threads.  Its transcendental
+// functions bound it, and one wavefront per row leaves a wave per SIMD at 1024
+// rows, whose latencies then show (1024 x 4096, two steps: 82 us, here 27).
+template <typename T>
+__global__ void __launch_bounds__(256) map_loss_kernel(LossArgs<T> a) {
+  __shared__ float red[2][4];
+  const int row = blockIdx.x, C = a.C;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const float* z = a.Z + (long)row * C;
+  const float* zd = a.dual ? a.Zd + (long)row * C : nullptr;
+  const float* t = a.targets + (long)row * C;
+  const float w = a.alpha_logits ? 1.0f / (1.0f + expf(-a.alpha_logits[row])) : 1.0f;
+  float loss = 0.0f, ldot = 0.0f;
+  for (int c = threadIdx.x; c < C; c += 256) {
+    float d, dd;
+    map_loss_elem(a, z[c], zd ? zd[c] : 0.0f, t[c], w * a.inv_n, d, dd, loss, ldot);
+    a.d[(long)row * a.ld + c] = Elem<T>::from_float(d);
+    if (a.dual) a.dd[(long)row * a.ld + c] = Elem<T>::from_float(dd);
+  }
+  for (int c = C + threadIdx.x; c < a.pad_to; c += 256) {
+    a.d[(long)row * a.ld + c] = Elem<T>::from_float(0.0f);
+    if (a.dual) a.dd[(long)row * a.ld + c] = Elem<T>::from_float(0.0f);
+  }
+  loss = wave_sum(loss);
+  ldot = wave_sum(ldot);
+  if (lane == 0) {
+    red[0][wv] = loss;
+    red[1][wv] = ldot;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) loss_row_out(a, row, w, (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]),
+                                     (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
+}
+
+template <typename T>
 __global__ void __launch_bounds__(256) loss_kernel(LossArgs<T> a) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -363,36 +446,11 @@ __global__ void __launch_bounds__(256) loss_kernel(LossArgs<T> a) {
       }
     }
   } else if (a.loss == 2) {
-    // Squared error after the M-step map y_i = i (2 + sin y_{i-1})^cos y_{i-1},
-    // mean over the C outputs.  Per element the map's value y_M and its first
-    // and second derivatives in z are carried through the M steps in registers
-    // (with h = d/dy ln f_i = cos^2 y / (2 + sin y) - sin y ln(2 + sin y):
-    // f_i' = f_i h, f_i'' = f_i (h^2 + h')), so no step is stored.
     const float* t = a.targets + (long)row * C;
-    const float invC = 1.0f / (float)C;
     for (int c = lane; c < C; c += 64) {
-      float g = z[c], g1 = 1.0f, g2 = 0.0f;
-      for (int i = 1; i <= a.map_M; ++i) {
-        float sn, cs;
-        sincosf(g, &sn, &cs);
-        const float u = 2.0f + sn, lu = logf(u), iu = 1.0f / u;
-        const float f = (float)i * expf(cs * lu);
-        const float h = cs * cs * iu - sn * lu;
-        const float hp = -cs * lu - 3.0f * sn * cs * iu - cs * cs * cs * iu * iu;
-        const float f1 = f * h, f2 = f * (h * h + hp);
-        g2 = f2 * g1 * g1 + f1 * g2;
-        g1 = f1 * g1;
-        g = f;
-      }
-      const float r = g - t[c];
-      loss += r * r * invC;
-      float vd = 0.0f;
-      if (a.dual) {
-        const float zdc = zd[c];
-        ldot += 2.0f * invC * r * g1 * zdc;
-        vd = 2.0f * scale * invC * zdc * (g1 * g1 + r * g2);
-      }
-      put(c, 2.0f * scale * invC * r * g1, vd);
+      float d, dd;
+      map_loss_elem(a, z[c], zd ? zd[c] : 0.0f, t[c], scale, d, dd, loss, ldot);
+      put(c, d, dd);
     }
     loss = wave_sum(loss);
     ldot = wave_sum(ldot);
@@ -432,11 +490,7 @@ __global__ void __launch_bounds__(256) loss_kernel(LossArgs<T> a) {
     loss = wave_sum(loss);
     ldot = wave_sum(ldot);
   }
-  if (lane == 0) {
-    if (a.loss_rows) a.loss_rows[row] = loss;
-    if (a.mvp_rows) a.mvp_rows[row] = ldot * a.inv_n;
-    if (a.deta_rows) a.deta_rows[row] = w * (1.0f - w) * ldot * a.inv_n;
-  }
+  if (lane == 0) loss_row_out(a, row, w, loss, ldot);
 }
 
 // Deterministic single-workgroup weighted sum.
@@ -1305,7 +1359,12 @@ hipError_t loss_head(const LossArgs<T>& args, hipStream_t s) {
   // heads are transposed through LDS tiles afterwards.
   LossArgs<T> a = args;
   a.direct_t = a.C <= 128 ? 1 : 0;
-  hipLaunchKernelGGL(loss_kernel<T>, dim3(cdiv(a.rows, 4)), dim3(256), 0, s, a);
+  // the map loss on a workgroup per row where its C columns keep 256 threads busy
+  // and the transposed copies are made afterwards
+  if (a.loss == 2 && !a.direct_t && a.C >= 256)
+    hipLaunchKernelGGL(map_loss_kernel<T>, dim3(a.rows), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(loss_kernel<T>, dim3(cdiv(a.rows, 4)), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.direct_t) return e;
   // transposed copies of dL/dz (and its tangent), coalesced through LDS
