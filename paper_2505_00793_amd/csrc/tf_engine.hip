@@ -48,15 +48,6 @@ constexpr int MAXB = 16;
 
 struct Lay {
   int d, H, dh, F, V, S, Bt, Bv, L, mh, VE, fused, remat;
-  // Sets of per-block activations with block rematerialisation.  With fused
-  // attention a second set (12 F + 40 d bytes a token and some row values) saves
-  // one block forward in every backward, dual ones included (4 blocks, 4096
-  // tokens, T = 8: 55.5 -> 53.0 ms; 4096-token contexts: 37.9 -> 35.9 ms).  It is
-  // taken where the plan stays no larger than one that also keeps a transposed
-  // copy of every weight-gradient and attention operand and float32 per-head
-  // gradients (4 V + 4 max(F, 3 d) + 4 F + 60 d bytes a token); materialised
-  // attention's S^2 buffers would cost more than the time.
-  int sets;
   float eps, lr;
   double base;
   long emb, ln1g[MAXB], ln1b[MAXB], wqkv[MAXB], wo[MAXB], ln2g[MAXB], ln2b[MAXB], w1[MAXB],
@@ -84,7 +75,6 @@ Lay make_lay(const mfmg_problem_desc& D) {
   y.VE = D.precision == MFMG_PREC_BF16 ? 8 : 4;
   y.fused = D.fused_attention;
   y.remat = D.block_remat;
-  y.sets = y.fused && (long)y.V + std::max(y.F, 3 * y.d) + 5 * y.d >= 2L * y.F + 2 * y.H + 16 ? 2 : 1;
   y.eps = D.ln_eps;
   y.lr = D.sgd_lr;
   y.base = D.rope_base;
@@ -207,24 +197,23 @@ void carve_act(const Lay& y, Carver& c, Act<T>& a) {
     a.hd[k] = F32(N * d);
   }
   // Per-block activations: one set per block, or with block rematerialisation
-  // one or two sets (y.sets) that the blocks' (re)computed forwards fill in turn,
-  // so that as many last blocks' activations survive the forward.
+  // one set that every block's (re)computed forward fills in turn.
   for (int b = 0; b < y.L; ++b) {
-    if (y.remat && b >= y.sets) {
-      a.xh1[b] = a.xh1[b - y.sets]; a.xhd1[b] = a.xhd1[b - y.sets]; a.rs1[b] = a.rs1[b - y.sets]; a.c1[b] = a.c1[b - y.sets];
-      a.xh2[b] = a.xh2[b - y.sets]; a.xhd2[b] = a.xhd2[b - y.sets]; a.rs2[b] = a.rs2[b - y.sets]; a.c2[b] = a.c2[b - y.sets];
-      a.a1[b] = a.a1[b - y.sets]; a.a1T[b] = a.a1T[b - y.sets]; a.a1d[b] = a.a1d[b - y.sets]; a.a1dT[b] = a.a1dT[b - y.sets];
-      a.a2[b] = a.a2[b - y.sets]; a.a2T[b] = a.a2T[b - y.sets]; a.a2d[b] = a.a2d[b - y.sets]; a.a2dT[b] = a.a2dT[b - y.sets];
-      a.Q[b] = a.Q[b - y.sets]; a.QT[b] = a.QT[b - y.sets]; a.K[b] = a.K[b - y.sets]; a.KT[b] = a.KT[b - y.sets];
-      a.Vv[b] = a.Vv[b - y.sets]; a.VT[b] = a.VT[b - y.sets];
-      a.Qd[b] = a.Qd[b - y.sets]; a.QdT[b] = a.QdT[b - y.sets]; a.Kd[b] = a.Kd[b - y.sets]; a.KdT[b] = a.KdT[b - y.sets];
-      a.Vd[b] = a.Vd[b - y.sets]; a.VdT[b] = a.VdT[b - y.sets];
-      a.P32[b] = a.P32[b - y.sets]; a.Pd32[b] = a.Pd32[b - y.sets];
-      a.Pb[b] = a.Pb[b - y.sets]; a.PbT[b] = a.PbT[b - y.sets]; a.Pdb[b] = a.Pdb[b - y.sets]; a.PdbT[b] = a.PdbT[b - y.sets];
-      a.lse[b] = a.lse[b - y.sets]; a.cst[b] = a.cst[b - y.sets];
-      a.O[b] = a.O[b - y.sets]; a.OT[b] = a.OT[b - y.sets]; a.Od[b] = a.Od[b - y.sets]; a.OdT[b] = a.OdT[b - y.sets];
-      a.Z1[b] = a.Z1[b - y.sets]; a.Z1d[b] = a.Z1d[b - y.sets];
-      a.A1[b] = a.A1[b - y.sets]; a.A1T[b] = a.A1T[b - y.sets]; a.A1d[b] = a.A1d[b - y.sets]; a.A1dT[b] = a.A1dT[b - y.sets];
+    if (y.remat && b > 0) {
+      a.xh1[b] = a.xh1[0]; a.xhd1[b] = a.xhd1[0]; a.rs1[b] = a.rs1[0]; a.c1[b] = a.c1[0];
+      a.xh2[b] = a.xh2[0]; a.xhd2[b] = a.xhd2[0]; a.rs2[b] = a.rs2[0]; a.c2[b] = a.c2[0];
+      a.a1[b] = a.a1[0]; a.a1T[b] = a.a1T[0]; a.a1d[b] = a.a1d[0]; a.a1dT[b] = a.a1dT[0];
+      a.a2[b] = a.a2[0]; a.a2T[b] = a.a2T[0]; a.a2d[b] = a.a2d[0]; a.a2dT[b] = a.a2dT[0];
+      a.Q[b] = a.Q[0]; a.QT[b] = a.QT[0]; a.K[b] = a.K[0]; a.KT[b] = a.KT[0];
+      a.Vv[b] = a.Vv[0]; a.VT[b] = a.VT[0];
+      a.Qd[b] = a.Qd[0]; a.QdT[b] = a.QdT[0]; a.Kd[b] = a.Kd[0]; a.KdT[b] = a.KdT[0];
+      a.Vd[b] = a.Vd[0]; a.VdT[b] = a.VdT[0];
+      a.P32[b] = a.P32[0]; a.Pd32[b] = a.Pd32[0];
+      a.Pb[b] = a.Pb[0]; a.PbT[b] = a.PbT[0]; a.Pdb[b] = a.Pdb[0]; a.PdbT[b] = a.PdbT[0];
+      a.lse[b] = a.lse[0]; a.cst[b] = a.cst[0];
+      a.O[b] = a.O[0]; a.OT[b] = a.OT[0]; a.Od[b] = a.Od[0]; a.OdT[b] = a.OdT[0];
+      a.Z1[b] = a.Z1[0]; a.Z1d[b] = a.Z1d[0];
+      a.A1[b] = a.A1[0]; a.A1T[b] = a.A1T[0]; a.A1d[b] = a.A1d[0]; a.A1dT[b] = a.A1dT[0];
       continue;
     }
     a.xh1[b] = F32(N * d); a.xhd1[b] = F32(N * d); a.rs1[b] = F32(N); a.c1[b] = F32(N);
@@ -750,10 +739,10 @@ struct TfEng {
                    nullptr, nullptr, y.lnfg, y.lnfb, out ? out->lnf[0] : nullptr,
                    out ? out->lnf[1] : nullptr));
     for (int b = y.L - 1; b >= 0; --b) {
-      // block rematerialisation: the shared sets hold the last blocks' activations
-      // from the forward; every other block is recomputed from its input h[2b]
-      // before its backward
-      if (y.remat && b < y.L - y.sets) HC(block_forward(th, v, Bn, b, false, a));
+      // block rematerialisation: the shared buffers hold the last block's
+      // activations from the forward; every other block is recomputed from its
+      // input h[2b] before its backward
+      if (y.remat && b < y.L - 1) HC(block_forward(th, v, Bn, b, false, a));
       // ---- MLP: h_out = h_mid + GELU(a2 W1) W2
       HC(dh_operands(N, dual, a));
       HC(gemm_param<T>(wsk(op(a.A1T[b], dual ? a.A1dT[b] : nullptr, a.dhbT, dual ? a.dhdbT : nullptr,
