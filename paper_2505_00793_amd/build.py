@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmfmg.so")
-GEMM_PARTS = 8   # gemm.hip is compiled in parts (its kernel instances), side by side
+GEMM_PARTS = 9   # gemm.hip is compiled in parts (its kernel instances), side by side
 SOURCES = ["gemm.hip", "elementwise.hip", "linreg.hip", "transformer.hip", "attention.hip", "tf_engine.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

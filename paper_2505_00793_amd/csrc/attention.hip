@@ -249,6 +249,7 @@ __global__ void __launch_bounds__(RB * 4, RB == 64 ? (DUAL ? 2 : 3) : (DUAL ? 1 
     }
     store4(a.O + tok * a.ldO + col, ov[0], ov[1], ov[2], ov[3]);
     if (DUAL) store4(a.Od + tok * a.ldO + col, odv[0], odv[1], odv[2], odv[3]);
+    if (!a.OT) continue;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       a.OT[(long)(col + r) * a.ldOT + tok] = f2bf(ov[r]);

@@ -1358,7 +1358,7 @@ hipError_t loss_head(const LossArgs<T>& args, hipStream_t s) {
   // wave's C strided stores per row cost less than a transpose launch); wider
   // heads are transposed through LDS tiles afterwards.
   LossArgs<T> a = args;
-  a.direct_t = a.C <= 128 ? 1 : 0;
+  a.direct_t = a.dT && a.C <= 128 ? 1 : 0;
   // the map loss on a workgroup per row where its C columns keep 256 threads busy
   // and the transposed copies are made afterwards
   if (a.loss == 2 && !a.direct_t && a.C >= 256)
@@ -1366,7 +1366,7 @@ hipError_t loss_head(const LossArgs<T>& args, hipStream_t s) {
   else
     hipLaunchKernelGGL(loss_kernel<T>, dim3(cdiv(a.rows, 4)), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.direct_t) return e;
+  if (e != hipSuccess || a.direct_t || !a.dT) return e;
   // transposed copies of dL/dz (and its tangent), coalesced through LDS
   const dim3 tg(cdiv(a.C, 64), cdiv(a.rows, 64), 2);
   if constexpr (sizeof(T) == 2) {

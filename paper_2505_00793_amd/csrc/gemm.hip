@@ -7,20 +7,21 @@
 //   dual forward          Z  = A W,       Zd  = Ad W + A Wd
 //   dual backward-data    dA = dZ W^T,    dAd = dZd W^T + dZ Wd^T
 //   dual backward-weight  G  = A^T dZ,    Gd  = Ad^T dZ + A^T dZd   (= H v)
-// All operands are stored with the contraction index contiguous (the
-// producers write both layouts), so tiles go from HBM to LDS with 16-byte
-// loads and from LDS to the MFMA units with 16-byte reads and no transposes.
+// Operands are stored with the contraction index contiguous (the MLP's producers
+// write both layouts), so tiles go from HBM to LDS with 16-byte loads and from LDS
+// to the MFMA units with 16-byte reads and no transposes; a transformer's weight
+// gradients take theirs as stored by token and transpose on the way out of LDS.
 // Tiles of A, Ad, B, Bd are staged together in LDS, so each HBM read of a
 // weight tile serves the primal and the tangent product.
 //
 // Matrix cores: v_mfma_f32_16x16x32_bf16 (bf16 operands) or
 // v_mfma_f32_16x16x4_f32 (float32 operands), 64-lane wavefronts, four
 // computing waves per workgroup in a 2 x 2 arrangement.  Two main loops:
-//   gemm_nt_ws  bf16 operands with k, leading dimensions and strides multiples
-//               of 8: a 2- to 4-stage LDS ring of 64-deep k steps filled by
+//   gemm_nt_ws  operands with k, leading dimensions and strides multiples of 16
+//               bytes (or bf16 ones stored k-major): a 2- to 4-stage LDS ring of 64-deep k steps filled by
 //               buffer_load ... lds from four loader waves while four waves
 //               multiply (512 threads);
-//   gemm_nt     everything else (float32, ragged k): register-staged,
+//   gemm_nt     everything else (ragged k, 16 columns): register-staged,
 //               double-buffered LDS, 256 threads.
 // Both end in the same staged epilogue.  Backward-weight products with few
 // output tiles and a long k can run split-K (batched partial products into a
@@ -181,7 +182,7 @@ struct ActFwdOp {
   int M, N;
   static constexpr bool PRELOAD = false;
   typedef int In;
-  __device__ int n_trans() const { return e.last ? 0 : (e.dual ? 2 : 1); }
+  __device__ int n_trans() const { return e.last || !e.AoT ? 0 : (e.dual ? 2 : 1); }
   __device__ __forceinline__ void row(int bz, int m, int n, int cnt, const float* c1,
                                       const float* c2, float* t1, float* t2) const {
     const bool vec = cnt == 4 && (e.N & 3) == 0;
@@ -229,7 +230,7 @@ struct ActBwdOp {
   struct In {
     float z[4], zd[4];
   };
-  __device__ int n_trans() const { return e.dual ? 2 : 1; }
+  __device__ int n_trans() const { return !e.dZT ? 0 : e.dual ? 2 : 1; }
   __device__ bool aligned() const { return (e.N & 3) == 0; }
   // 4 consecutive activations a[m][n..n+3] (n a multiple of 4) as floats
   __device__ __forceinline__ void ld_act4(long idx, float* out) const {
@@ -472,7 +473,7 @@ struct HeadMergeOp {
   int M, N;
   static constexpr bool PRELOAD = false;
   typedef int In;
-  __device__ int n_trans() const { return e.dual ? 2 : 1; }
+  __device__ int n_trans() const { return !e.OT ? 0 : e.dual ? 2 : 1; }
   __device__ __forceinline__ void row(int bz, int m, int n, int cnt, const float* c1,
                                       const float* c2, float* t1, float* t2) const {
     const long r = (long)(bz / e.heads) * e.seq + m;
@@ -499,7 +500,7 @@ struct HeadSplitOp {
   int M, N;
   static constexpr bool PRELOAD = false;
   typedef int In;
-  __device__ int n_trans() const { return e.dual ? 2 : 1; }
+  __device__ int n_trans() const { return !e.OhT ? 0 : e.dual ? 2 : 1; }
   __device__ __forceinline__ void row(int bz, int m, int n, int cnt, const float* c1,
                                       const float* c2, float* t1, float* t2) const {
     const int b = m / e.seq, s = m % e.seq;
@@ -1070,6 +1071,71 @@ struct DmaTile {
   }
 };
 
+// The same for an operand stored with the contraction index outermost (K-major:
+// [K][ld], COLS of its columns form the tile), bf16 only.  A k step is 64 rows of
+// COLS elements; the fragments are read from it by transposing LDS reads
+// (kfrag), which take 32 bytes of k rows 0..3 and 8..11 at once (and so on), so
+// the pairs of 16-byte chunks are XOR-swizzled by bits 0, 1 and 3 of the row: those
+// 8 rows then cover all 64 banks.  Rows past K read zero through the descriptor's range check; columns
+// between the operand's width and its leading dimension reach only outputs past
+// the edge of C.
+template <int COLS>
+__device__ __forceinline__ constexpr int kswizzle(int r) {
+  return 2 * (((r & 3) | ((r >> 3) & 1) << 2) / (128 / COLS));
+}
+template <int COLS>
+struct DmaTileK {
+  static constexpr int CPK = COLS / 8;        // 16-byte chunks per k row
+  static constexpr int RPB = 64 / CPK;        // k rows per 1 KB load
+  static constexpr int BPW = 64 / RPB / 4;    // loads per wave per k step
+  __amdgpu_buffer_rsrc_t rsrc;
+  unsigned row_off[BPW];   // byte offset of the lane's chunk in k step 0, or 2^31
+  unsigned ldb;            // bytes per k row
+
+  __device__ __forceinline__ void init(const bf16_t* base, int cols, int ld, int K, int col0,
+                                       int w) {
+    const unsigned bytes = (unsigned)(((long)(K - 1) * ld + ((cols + 7) & ~7)) * 2);
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)bytes, 0x00020000);
+    const int lane = threadIdx.x & 63;
+    ldb = (unsigned)ld * 2;
+#pragma unroll
+    for (int c = 0; c < BPW; ++c) {
+      const int r = (c * 4 + w) * RPB + lane / CPK;
+      const int col = col0 + ((lane % CPK) ^ kswizzle<COLS>(r)) * 8;
+      row_off[c] = col < cols ? (unsigned)r * ldb + (unsigned)col * 2 : 0x80000000u;
+    }
+  }
+  __device__ __forceinline__ void issue(char* dst, int k0, int, int w) const {
+#pragma unroll
+    for (int c = 0; c < BPW; ++c) {
+      const unsigned off =
+          row_off[c] != 0x80000000u ? row_off[c] + (unsigned)k0 * ldb : 0x80000000u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)(dst + (c * 4 + w) * 1024), 16,
+                                               off, 0, 0, 0);
+    }
+  }
+};
+
+// Fragment of 16 columns x 32 k values (rows kr .. kr + 31 of a K-major tile) by
+// two transposing reads.  ds_read_b64_tr_b16 works on groups of 16 lanes: lane i
+// of a group reads 4 consecutive elements at its own address, and lane j gets
+// element j % 4 of lanes j / 4, j / 4 + 4, + 8, + 12.  With lane i at row i / 4 and
+// columns 4 (i % 4) .. + 3, lane j so holds 4 rows of column j.  Group g takes
+// rows 8 g .. 8 g + 7 in its two reads: the k order of the other kernels, and so
+// the same bits.
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4s lds_v4s;
+template <int COLS>
+__device__ __forceinline__ bf16x8 kfrag(const char* p) {
+  union {
+    v4s h[2];
+    bf16x8 v;
+  } u;
+  u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
+  u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + 4 * COLS * 2));
+  return u.v;
+}
+
 // ------------------------------------------------------------------------------------
 // Main loop, warp-specialised (bfloat16, 512 threads).  A wave that issues a
 // global load stalls until the compute unit's load unit takes it (about 16
@@ -1078,8 +1144,9 @@ struct DmaTile {
 // and waves 0..3 only read fragments and multiply, so each SIMD has one wave
 // that keeps its matrix core busy while the other waits on the load unit.  The
 // eight waves meet at one barrier per k step and all of them walk the epilogue.
+// KM: both operands K-major, C1 = A^T B of A [K][lda], B [K][ldb] (and tangents).
 // ------------------------------------------------------------------------------------
-template <typename T, int FLAGS, int BM, int BN, int NST, class Epi>
+template <typename T, int FLAGS, int BM, int BN, int NST, class Epi, bool KM>
 __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<T>& op, const Epi& epi, int pid,
                                              int bz, char* smem) {
   constexpr int BK = DmaShape<T, FLAGS>::BK;
@@ -1111,8 +1178,8 @@ __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<T>& op, const Ep
   // staging buffer and one when the staged tile is complete.
   if (wave >= 4) {
     const int pw = wave - 4;
-    DmaTile<T, BM, CPR> tA, tAd;
-    DmaTile<T, BN, CPR> tB, tBd;
+    std::conditional_t<KM, DmaTileK<BM>, DmaTile<T, BM, CPR>> tA, tAd;
+    std::conditional_t<KM, DmaTileK<BN>, DmaTile<T, BN, CPR>> tB, tBd;
     if constexpr (SM::LA) tA.init(op.A + bz * op.sA, op.M, op.lda, K, m0, pw);
     if constexpr (SM::LAD) tAd.init(op.Ad + bz * op.sA, op.M, op.lda, K, m0, pw);
     if constexpr (SM::LB) tB.init(op.B + bz * op.sB, op.N, op.ldb, K, n0, pw);
@@ -1132,7 +1199,7 @@ __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<T>& op, const Ep
     // of the B and Bd rows, btpr threads per row, each over its 16-byte chunks
     // in their order in LDS; the btpr partial sums of a row are then combined in
     // lane order.  The entries' epilogue inputs are loaded before the loop.
-    constexpr bool BIAS = IsParamOp<Epi>::value && (SM::LB || SM::LBD);
+    constexpr bool BIAS = !KM && IsParamOp<Epi>::value && (SM::LB || SM::LBD);
     const int lt = tid - 256;
     bool bias_w = false;
     int brow = 0, btpr = 1, bcpt = CPR;
@@ -1205,6 +1272,19 @@ __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<T>& op, const Ep
     int foff[NCH];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) foff[c] = (lane & 15) * ROWB + (((lane >> 4) + 4 * c) ^ sw) * 16;
+    // K-major tiles: the lane's k row and 8 bytes of it, for each 16-column slab
+    int ka[TM], kb[TN];
+    if constexpr (KM) {
+      const int kr = (lane >> 4) * 8 + ((lane >> 2) & 3);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        ka[i] = kr * BM * 2 + ((((wm * TM + i) * 2) ^ kswizzle<BM>(kr)) + ((lane >> 1) & 1)) * 16 +
+                (lane & 1) * 8;
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        kb[j] = kr * BN * 2 + ((((wn * TN + j) * 2) ^ kswizzle<BN>(kr)) + ((lane >> 1) & 1)) * 16 +
+                (lane & 1) * 8;
+    }
     for (int kt = 0; kt < nk; ++kt) {
       wait_vm_lgkm<0>();   // reads of step kt - 1 done: its stage may be refilled
       lds_barrier();       // every load of step kt has landed
@@ -1224,15 +1304,27 @@ __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<T>& op, const Ep
         for (int f = 0; f < NF; ++f) {
 #pragma unroll
           for (int i = 0; i < TM; ++i) {
-            const int r0 = (wm * WTM + i * 16) * ROWB + foff[c0 + f];
-            if constexpr (SM::LA) a[f][i] = *reinterpret_cast<const frag_t*>(As + r0);
-            if constexpr (HAD) ad[f][i] = *reinterpret_cast<const frag_t*>(Ads + r0);
+            if constexpr (KM) {
+              const int r0 = ka[i] + (c0 + f) * 32 * BM * 2;
+              if constexpr (SM::LA) a[f][i] = kfrag<BM>(As + r0);
+              if constexpr (HAD) ad[f][i] = kfrag<BM>(Ads + r0);
+            } else {
+              const int r0 = (wm * WTM + i * 16) * ROWB + foff[c0 + f];
+              if constexpr (SM::LA) a[f][i] = *reinterpret_cast<const frag_t*>(As + r0);
+              if constexpr (HAD) ad[f][i] = *reinterpret_cast<const frag_t*>(Ads + r0);
+            }
           }
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
-            const int r0 = (wn * WTN + j * 16) * ROWB + foff[c0 + f];
-            if constexpr (SM::LB) b[f][j] = *reinterpret_cast<const frag_t*>(Bs + r0);
-            if constexpr (HBD) bd[f][j] = *reinterpret_cast<const frag_t*>(Bds + r0);
+            if constexpr (KM) {
+              const int r0 = kb[j] + (c0 + f) * 32 * BN * 2;
+              if constexpr (SM::LB) b[f][j] = kfrag<BN>(Bs + r0);
+              if constexpr (HBD) bd[f][j] = kfrag<BN>(Bds + r0);
+            } else {
+              const int r0 = (wn * WTN + j * 16) * ROWB + foff[c0 + f];
+              if constexpr (SM::LB) b[f][j] = *reinterpret_cast<const frag_t*>(Bs + r0);
+              if constexpr (HBD) bd[f][j] = *reinterpret_cast<const frag_t*>(Bds + r0);
+            }
           }
         }
 #pragma unroll
@@ -1256,11 +1348,11 @@ __device__ __forceinline__ void gemm_ws_tile(const GemmOperands<T>& op, const Ep
   walk_tile<FLAGS, BN, BM, 512>(S1, S2, m0, n0, bz, epi);
 }
 
-template <typename T, int FLAGS, int BM, int BN, int NST, class Epi>
+template <typename T, int FLAGS, int BM, int BN, int NST, class Epi, bool KM = false>
 __global__ void __launch_bounds__(512) gemm_nt_ws(GemmOperands<T> op, Epi epi) {
   __shared__ __attribute__((aligned(1024))) char
       smem[DmaSmem<T, FLAGS, BM, BN, DmaShape<T, FLAGS>::BK, NST, 1>::BYTES];
-  gemm_ws_tile<T, FLAGS, BM, BN, NST, Epi>(op, epi, (int)blockIdx.x, (int)blockIdx.y, smem);
+  gemm_ws_tile<T, FLAGS, BM, BN, NST, Epi, KM>(op, epi, (int)blockIdx.x, (int)blockIdx.y, smem);
 }
 
 // Two independent products in one launch, for products too small to fill the
@@ -1291,9 +1383,9 @@ __global__ void __launch_bounds__(512) gemm_pair_ws(GemmOperands<bf16_t> op1, E1
     j = which == 0 ? cyc * g1 + r : cyc * g2 + (r - rest1);
   }
   if (which == 0)
-    gemm_ws_tile<bf16_t, F1, BM1, BN1, NST1, E1>(op1, epi1, j, 0, smem);
+    gemm_ws_tile<bf16_t, F1, BM1, BN1, NST1, E1, false>(op1, epi1, j, 0, smem);
   else
-    gemm_ws_tile<bf16_t, F2, BM2, BN2, NST2, E2>(op2, epi2, j, 0, smem);
+    gemm_ws_tile<bf16_t, F2, BM2, BN2, NST2, E2, false>(op2, epi2, j, 0, smem);
 }
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -1349,6 +1441,25 @@ bool dma_ok(const GemmOperands<T>& op) {
          dma_operand_ok(op.Ad, op.M, op.lda, op.K, op.sA) &&
          dma_operand_ok(op.B, op.N, op.ldb, op.K, op.sB) &&
          dma_operand_ok(op.Bd, op.N, op.ldb, op.K, op.sB);
+}
+
+// K-major operands the direct-to-LDS loads can address (any K).
+bool km_ok(const GemmOperands<bf16_t>& o) {
+  auto ok = [&](const bf16_t* p, int cols, int ld, long stride) {
+    return !p || (!(reinterpret_cast<uintptr_t>(p) & 15) && ld % 8 == 0 && ld < (1 << 20) &&
+                  ld >= cols && stride % 8 == 0 && ((long)o.K * ld) * 2 < (1L << 31));
+  };
+  return o.K > 0 && ok(o.A, o.M, o.lda, o.sA) && ok(o.Ad, o.M, o.lda, o.sA) &&
+         ok(o.B, o.N, o.ldb, o.sB) && ok(o.Bd, o.N, o.ldb, o.sB);
+}
+
+template <int FLAGS, int BM, int BN, class Epi>
+hipError_t launch_km(const GemmOperands<bf16_t>& op, const Epi& epi, hipStream_t s) {
+  const dim3 grid(cdiv(op.M, BM) * cdiv(op.N, BN), op.batch);
+  constexpr int NST = DmaDepth<bf16_t, FLAGS, BM, BN, 147456>::NST;
+  hipLaunchKernelGGL((gemm_nt_ws<bf16_t, FLAGS, BM, BN, NST, Epi, true>), grid, dim3(512), 0, s,
+                     op, epi);
+  return hipGetLastError();
 }
 
 template <typename T, int FLAGS, int BM, int BN, class Epi>
@@ -1487,22 +1598,24 @@ __global__ void __launch_bounds__(256) splitk_epilogue(const float* __restrict__
   }
 }
 
-template <typename T, int FLAGS, class Epi>
+template <typename T, int FLAGS, class Epi, bool KM = false>
 hipError_t launch_splitk(const GemmOperands<T>& op, const Epi& epi, int S, hipStream_t s) {
   constexpr bool HC2 = (FLAGS & (G_AD | G_BD)) != 0;
   const long MN = (long)op.M * op.N;
   GemmOperands<T> p = op;
   p.K = op.K / S;
   p.batch = S;
-  p.sA = p.K;
-  p.sB = p.K;
+  p.sA = KM ? (long)p.K * op.lda : p.K;
+  p.sB = KM ? (long)p.K * op.ldb : p.K;
   p.ws = nullptr;
   p.ws_floats = 0;
   EpiStore e;
   e.C = op.ws; e.Cd = op.ws + S * MN; e.ldc = op.N; e.sC = MN; e.scale = 1.0f;
   e.M = op.M; e.N = op.N; e.dual = HC2 ? 1 : 0;
   hipError_t r;
-  if (sizeof(T) == 2 && dma_ok(p))
+  if constexpr (KM)
+    r = launch_km<FLAGS, 128, 128>(p, StoreOp{e, op.M, op.N}, s);
+  else if (sizeof(T) == 2 && dma_ok(p))
     r = launch<T, FLAGS, 128, 128>(p, StoreOp{e, op.M, op.N}, s);
   else
     r = launch<T, FLAGS, 64, 64>(p, StoreOp{e, op.M, op.N}, s);
@@ -1554,6 +1667,26 @@ hipError_t launch_sized(const GemmOperands<T>& op, const Epi& epi, hipStream_t s
       return launch<T, FLAGS, 64, 32>(op, epi, s);
   }
   return launch<T, FLAGS, 64, 64>(op, epi, s);
+}
+
+// A weight gradient of K-major bf16 operands: split-K and tiles as launch_sized
+// picks them.  The products take about the time they take from transposed copies (35 us
+// for the dual 512 x 2048 gradient over 4096 tokens, four k slices), and the copies
+// are not made: on the 4-block decoder at 4096 tokens some 250 transposes a
+// meta-gradient and a quarter of the activation epilogues' bytes (55.3 -> 51.1 ms).
+template <int FLAGS>
+hipError_t launch_param_km(const GemmOperands<bf16_t>& op, const ParamOp<bf16_t>& epi,
+                           hipStream_t s) {
+  if (op.M <= 0 || op.N <= 0) return hipSuccess;
+  if (op.ws) {
+    const int S = splitk_count(op.M, op.N, op.K);
+    if (S > 1 && op.ws_floats >= 2L * S * op.M * op.N)
+      return launch_splitk<bf16_t, FLAGS, ParamOp<bf16_t>, true>(op, epi, S, s);
+  }
+  if (cdiv(op.M, 128) * cdiv(op.N, 128) >= 192) return launch_km<FLAGS, 128, 128>(op, epi, s);
+  if (cdiv(op.M, 128) * cdiv(op.N, 64) >= 192) return launch_km<FLAGS, 128, 64>(op, epi, s);
+  if (cdiv(op.M, 64) * cdiv(op.N, 64) >= 192) return launch_km<FLAGS, 64, 64>(op, epi, s);
+  return launch_km<FLAGS, 64, 32>(op, epi, s);
 }
 
 // The products each epilogue comes with; other flags are refused.
@@ -1686,6 +1819,17 @@ hipError_t gemm_param(const GemmOperands<T>& op, int flags, const ParamArgs<T>& 
   return dispatch(op, flags, ParamOp<T>{P, P.nin, P.nout}, s);
 }
 
+#if !defined(GEMM_PART) || GEMM_PART == 8
+hipError_t gemm_param_km(const GemmOperands<bf16_t>& op, int flags, const ParamArgs<bf16_t>& P,
+                         hipStream_t s) {
+  if (op.batch != 1 || P.b_off >= 0 || !km_ok(op)) return hipErrorInvalidValue;
+  const ParamOp<bf16_t> epi{P, P.nin, P.nout};
+  if (flags == G_C1) return launch_param_km<G_C1>(op, epi, s);
+  if (flags == (G_C1 | G_AD | G_BD)) return launch_param_km<G_C1 | G_AD | G_BD>(op, epi, s);
+  return hipErrorInvalidValue;
+}
+#endif
+
 template <typename T>
 hipError_t gemm_store(const GemmOperands<T>& op, int flags, const EpiStore& e, hipStream_t s) {
   return dispatch(op, flags, StoreOp{e, e.M, e.N}, s);
@@ -1705,7 +1849,7 @@ hipError_t gemm_head_split(const GemmOperands<T>& op, int flags, const EpiHeadSp
   return dispatch(op, flags, HeadSplitOp<T>{e, e.M, e.N}, s);
 }
 
-// Explicit instantiations.  The build compiles this file once per part (GEMM_PART = 0 .. 7), all
+// Explicit instantiations.  The build compiles this file once per part (GEMM_PART = 0 .. 8), all
 // parts at once; without GEMM_PART one translation unit holds everything.
 #if !defined(GEMM_PART) || GEMM_PART == 0
 template hipError_t gemm_param<bf16_t>(const GemmOperands<bf16_t>&, int, const ParamArgs<bf16_t>&, hipStream_t);

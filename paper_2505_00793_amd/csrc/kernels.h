@@ -61,7 +61,7 @@ struct EpiActFwd {
   int M, N;
   float* Z;              // [M][N]
   float* Zd;             // [M][N] (dual)
-  T* Ao;  T* AoT;        // [M][ldA], [N][ldAT]
+  T* Ao;  T* AoT;        // [M][ldA], [N][ldAT]; AoT (and AdoT) may be null
   T* Ado; T* AdoT;       // (dual)
   int ldA, ldAT;
   int zpad = 0;          // 1: columns N .. ldA - 1 (and M .. ldAT - 1) written as zero; both
@@ -81,7 +81,7 @@ struct EpiActBwd {
   int ldAp;
   int act, dual;
   int M, N;
-  T* dZ;  T* dZT;        // [M][ld], [N][ldT]
+  T* dZ;  T* dZT;        // [M][ld], [N][ldT]; dZT (and dZdT) may be null
   T* dZd; T* dZdT;
   int ld, ldT;
   int zpad = 0;          // as in EpiActFwd, for ld and ldT
@@ -110,7 +110,8 @@ struct EpiResid {
 
 // Attention output of head z = b * heads + h (rows = query positions s,
 // columns = head dims j) written as operands in token-major layout:
-// O[(b * seq + s) * ldO + h * dh + j] and the transpose OT[(h * dh + j) * ldOT + b * seq + s].
+// O[(b * seq + s) * ldO + h * dh + j] and the transpose OT[(h * dh + j) * ldOT + b * seq + s]
+// (OT and OdT may be null).
 template <typename T>
 struct EpiHeadMerge {
   T* O; T* OT; T* Od; T* OdT;
@@ -120,7 +121,8 @@ struct EpiHeadMerge {
 };
 
 // The inverse: a token-major [tokens][heads * dh] result written per head,
-// Oh[((b * heads + h) * seq + s) * ldh + j] and OhT[((b * heads + h) * dh + j) * ldhT + s].
+// Oh[((b * heads + h) * seq + s) * ldh + j] and OhT[((b * heads + h) * dh + j) * ldhT + s]
+// (OhT and OdhT may be null).
 template <typename T>
 struct EpiHeadSplit {
   T* Oh; T* OhT; T* Odh; T* OdhT;
@@ -185,7 +187,7 @@ struct LossArgs {
   const int* labels;        // CE
   const float* targets;     // MSE [rows][C]
   const float* alpha_logits;  // per-row weight logits, or null (weights 1)
-  T* d; T* dT;              // dL/dz in both layouts [rows][ld], [C][ldT]
+  T* d; T* dT;              // dL/dz [rows][ld] and its transpose [C][ldT], or dT null
   T* dd; T* ddT;            // its tangent (dual)
   int ld, ldT;
   int pad_to;               // columns C .. pad_to - 1 of d (dd) are written as zero
@@ -205,6 +207,12 @@ hipError_t gemm_act_bwd(const GemmOperands<T>& op, int flags, const EpiActBwd<T>
 template <typename T>
 hipError_t gemm_param(const GemmOperands<T>& op, int flags, const ParamArgs<T>& P,
                       hipStream_t s);
+// The same for operands stored with the contraction index outermost: C1 = A^T B
+// of A [K][lda], B [K][ldb] (and their tangents), for matrices without a bias
+// (P.b_off < 0); 16-byte aligned, leading dimensions multiples of 8, each operand
+// under 2 GB, any K.
+hipError_t gemm_param_km(const GemmOperands<bf16_t>& op, int flags, const ParamArgs<bf16_t>& P,
+                         hipStream_t s);
 // A layer's backward-weight product (with the parameter epilogue) and its
 // backward-data product (with the activation epilogue), which are independent:
 // gemm_pairs says whether both are small enough to share one launch (bf16

@@ -48,6 +48,9 @@ constexpr int MAXB = 16;
 
 struct Lay {
   int d, H, dh, F, V, S, Bt, Bv, L, mh, VE, fused, remat;
+  // the weight gradients read their operands as stored by token (gemm_param_km),
+  // so no transposed copies of them exist: bf16, every operand under 2 GB
+  bool km;
   float eps, lr;
   double base;
   long emb, ln1g[MAXB], ln1b[MAXB], wqkv[MAXB], wo[MAXB], ln2g[MAXB], ln2b[MAXB], w1[MAXB],
@@ -75,6 +78,7 @@ Lay make_lay(const mfmg_problem_desc& D) {
   y.VE = D.precision == MFMG_PREC_BF16 ? 8 : 4;
   y.fused = D.fused_attention;
   y.remat = D.block_remat;
+  y.km = y.VE == 8 && (long)y.maxB() * y.S * y.ld(std::max({3 * y.d, y.F, y.V})) * 2 < (1L << 31);
   y.eps = D.ln_eps;
   y.lr = D.sgd_lr;
   y.base = D.rope_base;
@@ -175,13 +179,16 @@ struct Act {  // one inner step at up to maxB sequences (the dynamic memory)
   float *cs, *sn;
 };
 
+// all: also the transposed weight-gradient operands
 template <typename T>
-void carve_act(const Lay& y, Carver& c, Act<T>& a) {
+void carve_act_bufs(const Lay& y, Carver& c, Act<T>& a, bool all) {
   const long N = (long)y.maxB() * y.S, d = y.d, F = y.F, S = y.S;
   const long BH = (long)y.maxB() * y.H;
   const long hrow = (long)S * y.ld(y.dh), hcol = (long)y.dh * y.ld(S);  // per-head operand sizes
   auto F32 = [&](long n) { return c.take<float>(n); };
   auto OPT = [&](long n) { return c.take<T>(n); };
+  // transposed weight-gradient operands
+  auto OPTW = [&](long n) -> T* { return all ? c.take<T>(n) : nullptr; };
   a.ids = c.take<int>(N);
   a.labels = c.take<int>(N);
   // The residual stream: h[2b] enters block b, h[2b + 1] is its middle (after
@@ -218,10 +225,10 @@ void carve_act(const Lay& y, Carver& c, Act<T>& a) {
     }
     a.xh1[b] = F32(N * d); a.xhd1[b] = F32(N * d); a.rs1[b] = F32(N); a.c1[b] = F32(N);
     a.xh2[b] = F32(N * d); a.xhd2[b] = F32(N * d); a.rs2[b] = F32(N); a.c2[b] = F32(N);
-    a.a1[b] = OPT(N * y.ld(d)); a.a1T[b] = OPT(d * y.ld(N));
-    a.a1d[b] = OPT(N * y.ld(d)); a.a1dT[b] = OPT(d * y.ld(N));
-    a.a2[b] = OPT(N * y.ld(d)); a.a2T[b] = OPT(d * y.ld(N));
-    a.a2d[b] = OPT(N * y.ld(d)); a.a2dT[b] = OPT(d * y.ld(N));
+    a.a1[b] = OPT(N * y.ld(d)); a.a1T[b] = OPTW(d * y.ld(N));
+    a.a1d[b] = OPT(N * y.ld(d)); a.a1dT[b] = OPTW(d * y.ld(N));
+    a.a2[b] = OPT(N * y.ld(d)); a.a2T[b] = OPTW(d * y.ld(N));
+    a.a2d[b] = OPT(N * y.ld(d)); a.a2dT[b] = OPTW(d * y.ld(N));
     a.Q[b] = OPT(BH * hrow); a.QT[b] = OPT(BH * hcol);
     a.K[b] = OPT(BH * hrow); a.KT[b] = OPT(BH * hcol);
     a.Vv[b] = OPT(BH * hrow); a.VT[b] = OPT(BH * hcol);
@@ -238,15 +245,15 @@ void carve_act(const Lay& y, Carver& c, Act<T>& a) {
       a.Pdb[b] = OPT(BH * S * y.ld(S)); a.PdbT[b] = OPT(BH * S * y.ld(S));
       a.lse[b] = a.cst[b] = nullptr;
     }
-    a.O[b] = OPT(N * y.ld(d)); a.OT[b] = OPT(d * y.ld(N));
-    a.Od[b] = OPT(N * y.ld(d)); a.OdT[b] = OPT(d * y.ld(N));
+    a.O[b] = OPT(N * y.ld(d)); a.OT[b] = OPTW(d * y.ld(N));
+    a.Od[b] = OPT(N * y.ld(d)); a.OdT[b] = OPTW(d * y.ld(N));
     a.Z1[b] = F32(N * F); a.Z1d[b] = F32(N * F);
-    a.A1[b] = OPT(N * y.ld(F)); a.A1T[b] = OPT(F * y.ld(N));
-    a.A1d[b] = OPT(N * y.ld(F)); a.A1dT[b] = OPT(F * y.ld(N));
+    a.A1[b] = OPT(N * y.ld(F)); a.A1T[b] = OPTW(F * y.ld(N));
+    a.A1d[b] = OPT(N * y.ld(F)); a.A1dT[b] = OPTW(F * y.ld(N));
   }
   a.xhf = F32(N * d); a.xhdf = F32(N * d); a.rsf = F32(N); a.cf = F32(N);
-  a.af = OPT(N * y.ld(d)); a.afT = OPT(d * y.ld(N));
-  a.afd = OPT(N * y.ld(d)); a.afdT = OPT(d * y.ld(N));
+  a.af = OPT(N * y.ld(d)); a.afT = OPTW(d * y.ld(N));
+  a.afd = OPT(N * y.ld(d)); a.afdT = OPTW(d * y.ld(N));
   a.logits = F32(N * y.V); a.logitsd = F32(N * y.V);
   a.y32 = F32(N * std::max(d, F)); a.yd32 = F32(N * std::max(d, F));
   a.qkv32 = F32(N * 3 * d); a.qkvd32 = F32(N * 3 * d);
@@ -263,14 +270,14 @@ void carve_act(const Lay& y, Carver& c, Act<T>& a) {
     a.dSd = OPT(BH * S * y.ld(S)); a.dSdT = OPT(BH * S * y.ld(S));
     a.ar = a.ard = nullptr;
   }
-  a.dz = OPT(N * y.ld(y.V)); a.dzT = OPT((long)y.V * y.ld(N));
-  a.dzd = OPT(N * y.ld(y.V)); a.dzdT = OPT((long)y.V * y.ld(N));
+  a.dz = OPT(N * y.ld(y.V)); a.dzT = OPTW((long)y.V * y.ld(N));
+  a.dzd = OPT(N * y.ld(y.V)); a.dzdT = OPTW((long)y.V * y.ld(N));
   a.dh = F32(N * d); a.dhd = F32(N * d);
-  a.dhb = OPT(N * y.ld(d)); a.dhbT = OPT(d * y.ld(N));
-  a.dhdb = OPT(N * y.ld(d)); a.dhdbT = OPT(d * y.ld(N));
+  a.dhb = OPT(N * y.ld(d)); a.dhbT = OPTW(d * y.ld(N));
+  a.dhdb = OPT(N * y.ld(d)); a.dhdbT = OPTW(d * y.ld(N));
   const long FQ = std::max(F, 3 * d);  // also holds the dqkv operands
-  a.dZ1 = OPT(N * y.ld(FQ)); a.dZ1T = OPT(FQ * y.ld(N));
-  a.dZ1d = OPT(N * y.ld(FQ)); a.dZ1dT = OPT(FQ * y.ld(N));
+  a.dZ1 = OPT(N * y.ld(FQ)); a.dZ1T = OPTW(FQ * y.ld(N));
+  a.dZ1d = OPT(N * y.ld(FQ)); a.dZ1dT = OPTW(FQ * y.ld(N));
   a.dOh = OPT(BH * hrow); a.dOhT = OPT(BH * hcol);
   a.dOdh = OPT(BH * hrow); a.dOdhT = OPT(BH * hcol);
   a.lnpart = F32((long)ln_bwd_parts((int)N) * 4 * d);
@@ -284,6 +291,17 @@ void carve_act(const Lay& y, Carver& c, Act<T>& a) {
   a.loss_rows = F32(N);
   a.cs = F32((long)S * y.dh / 2);
   a.sn = F32((long)S * y.dh / 2);
+}
+
+// A step's dynamic memory: the size callers are given is that of every buffer,
+// whichever of them the plan uses.
+template <typename T>
+void carve_act(const Lay& y, Carver& c, Act<T>& a) {
+  Carver size{nullptr, c.off};
+  Act<T> none;
+  carve_act_bufs(y, size, none, true);
+  carve_act_bufs(y, c, a, !y.km);
+  c.off = size.off;
 }
 
 // Meta-model buffers for R token rows.
@@ -384,6 +402,22 @@ struct TfEng {
     o.ws_floats = a.skws_n;
     return o;
   }
+  // Weight gradient (and its tangent) of a matrix with input rows (A, Ad) [N][ld(in)]
+  // and output gradient (dZ, dZd) [N][ld(out)] from those rows, or from their
+  // transposes where the plan has them.
+  hipError_t wgrad(const T* A, const T* Ad, const T* AT, const T* AdT, const T* dZ, const T* dZd,
+                   const T* dZT, const T* dZdT, int in, int out, int N, bool dual,
+                   const ParamArgs<T>& P, const Act<T>& a) const {
+    if constexpr (std::is_same<T, bf16_t>::value) {
+      if (y.km)
+        return gemm_param_km(wsk(op(A, dual ? Ad : nullptr, dZ, dual ? dZd : nullptr,
+                                    (int)y.ld(in), (int)y.ld(out), in, out, N), a),
+                             fl(dual), P, s);
+    }
+    return gemm_param<T>(wsk(op(AT, dual ? AdT : nullptr, dZT, dual ? dZdT : nullptr, (int)y.ld(N),
+                                (int)y.ld(N), in, out, N), a),
+                         fl(dual), P, s);
+  }
   // Operands of block b's fused attention (bf16 only: the option is rejected
   // for float32 operands before any plan is made).
   AttnArgs attn_args(int b, int Bn, bool dual, const Act<T>& a) const {
@@ -445,6 +479,7 @@ struct TfEng {
       if (ln_direct(ln.N)) {
         ln.yb = row; ln.ydb = dual ? rowd : nullptr; ln.ldb = (int)y.ld(y.d);
         HC(ln_fwd(ln, s));
+        if (y.km) return hipSuccess;
         return transpose_bf16(row, dual ? rowd : nullptr, ln.N, y.d, (int)y.ld(y.d), tr,
                               dual ? trd : nullptr, (int)y.ld(ln.N), s);
       }
@@ -456,6 +491,7 @@ struct TfEng {
   // after the LayerNorm backward that produced it.
   hipError_t dh_operands(int N, bool dual, const Act<T>& a) const {
     if constexpr (std::is_same<T, bf16_t>::value) {
+      if (ln_direct(N) && y.km) return hipSuccess;
       if (ln_direct(N))
         return transpose_bf16(a.dhb, dual ? a.dhdb : nullptr, N, y.d, (int)y.ld(y.d), a.dhbT,
                               dual ? a.dhdbT : nullptr, (int)y.ld(N), s);
@@ -729,9 +765,8 @@ struct TfEng {
       return ln_bwd<T>(l, goff, boff, P, og, ob, s);
     };
     // unembedding
-    HC(gemm_param<T>(wsk(op(a.afT, dual ? a.afdT : nullptr, a.dzT, dual ? a.dzdT : nullptr,
-                        (int)y.ld(N), (int)y.ld(N), d, y.V, N), a),
-                     fl(dual), matP(y.unemb, d, y.V, out ? out->U : nullptr, out ? out->UT : nullptr), s));
+    HC(wgrad(a.af, a.afd, a.afT, a.afdT, a.dz, a.dzd, a.dzT, a.dzdT, d, y.V, N, dual,
+             matP(y.unemb, d, y.V, out ? out->U : nullptr, out ? out->UT : nullptr), a));
     HC(store(op(a.dz, dual ? a.dzd : nullptr, th.U, dual ? v->U : nullptr, (int)y.ld(y.V),
                 (int)y.ld(y.V), N, d, y.V),
              fl(dual), a.y32, a.yd32, d, 0, 1.0f, dual));
@@ -745,9 +780,8 @@ struct TfEng {
       if (y.remat && b < y.L - 1) HC(block_forward(th, v, Bn, b, false, a));
       // ---- MLP: h_out = h_mid + GELU(a2 W1) W2
       HC(dh_operands(N, dual, a));
-      HC(gemm_param<T>(wsk(op(a.A1T[b], dual ? a.A1dT[b] : nullptr, a.dhbT, dual ? a.dhdbT : nullptr,
-                          (int)y.ld(N), (int)y.ld(N), F, d, N), a),
-                       fl(dual), matP(y.w2[b], F, d, out ? out->W[b][3] : nullptr, out ? out->WT[b][3] : nullptr), s));
+      HC(wgrad(a.A1[b], a.A1d[b], a.A1T[b], a.A1dT[b], a.dhb, a.dhdb, a.dhbT, a.dhdbT, F, d, N, dual,
+               matP(y.w2[b], F, d, out ? out->W[b][3] : nullptr, out ? out->WT[b][3] : nullptr), a));
       {
         EpiActBwd<T> e;
         e.Zp = a.Z1[b]; e.Zdp = a.Z1d[b]; e.Ap = nullptr; e.ldAp = 0;
@@ -758,9 +792,8 @@ struct TfEng {
                               (int)y.ld(d), (int)y.ld(d), N, F, d),
                            fl(dual), e, s));
       }
-      HC(gemm_param<T>(wsk(op(a.a2T[b], dual ? a.a2dT[b] : nullptr, a.dZ1T, dual ? a.dZ1dT : nullptr,
-                          (int)y.ld(N), (int)y.ld(N), d, F, N), a),
-                       fl(dual), matP(y.w1[b], d, F, out ? out->W[b][2] : nullptr, out ? out->WT[b][2] : nullptr), s));
+      HC(wgrad(a.a2[b], a.a2d[b], a.a2T[b], a.a2dT[b], a.dZ1, a.dZ1d, a.dZ1T, a.dZ1dT, d, F, N, dual,
+               matP(y.w1[b], d, F, out ? out->W[b][2] : nullptr, out ? out->WT[b][2] : nullptr), a));
       HC(store(op(a.dZ1, dual ? a.dZ1d : nullptr, th.W[b][2], dual ? v->W[b][2] : nullptr,
                   (int)y.ld(F), (int)y.ld(F), N, d, F),
                fl(dual), a.y32, a.yd32, d, 0, 1.0f, dual));
@@ -769,9 +802,8 @@ struct TfEng {
                      out ? out->ln[b][2] : nullptr, out ? out->ln[b][3] : nullptr));
       // ---- attention: h_mid = h + Attn(LN1(h)) Wo
       HC(dh_operands(N, dual, a));
-      HC(gemm_param<T>(wsk(op(a.OT[b], dual ? a.OdT[b] : nullptr, a.dhbT, dual ? a.dhdbT : nullptr,
-                          (int)y.ld(N), (int)y.ld(N), d, d, N), a),
-                       fl(dual), matP(y.wo[b], d, d, out ? out->W[b][1] : nullptr, out ? out->WT[b][1] : nullptr), s));
+      HC(wgrad(a.O[b], a.Od[b], a.OT[b], a.OdT[b], a.dhb, a.dhdb, a.dhbT, a.dhdbT, d, d, N, dual,
+               matP(y.wo[b], d, d, out ? out->W[b][1] : nullptr, out ? out->WT[b][1] : nullptr), a));
       {
         EpiHeadSplit<T> e;
         e.Oh = a.dOh; e.OhT = a.dOhT; e.Odh = a.dOdh; e.OdhT = a.dOdhT;
@@ -833,16 +865,16 @@ struct TfEng {
       }
       HC(rope_merge(r, s));
       if (direct) {
-        if constexpr (std::is_same<T, bf16_t>::value)
+        if constexpr (std::is_same<T, bf16_t>::value) if (!y.km)
           HC(transpose_bf16(a.dZ1, dual ? a.dZ1d : nullptr, N, 3 * d, (int)y.ld(3 * d), a.dZ1T,
                             dual ? a.dZ1dT : nullptr, (int)y.ld(N), s));
       } else {
         HC(convs({{a.qkv32, a.dZ1, a.dZ1T}, {dual ? a.qkvd32 : nullptr, a.dZ1d, a.dZ1dT}}, N,
                  3 * d));
       }
-      HC(gemm_param<T>(wsk(op(a.a1T[b], dual ? a.a1dT[b] : nullptr, a.dZ1T, dual ? a.dZ1dT : nullptr,
-                          (int)y.ld(N), (int)y.ld(N), d, 3 * d, N), a),
-                       fl(dual), matP(y.wqkv[b], d, 3 * d, out ? out->W[b][0] : nullptr, out ? out->WT[b][0] : nullptr), s));
+      HC(wgrad(a.a1[b], a.a1d[b], a.a1T[b], a.a1dT[b], a.dZ1, a.dZ1d, a.dZ1T, a.dZ1dT, d, 3 * d, N,
+               dual,
+               matP(y.wqkv[b], d, 3 * d, out ? out->W[b][0] : nullptr, out ? out->WT[b][0] : nullptr), a));
       HC(store(op(a.dZ1, dual ? a.dZ1d : nullptr, th.W[b][0], dual ? v->W[b][0] : nullptr,
                   (int)y.ld(3 * d), (int)y.ld(3 * d), N, d, 3 * d),
                fl(dual), a.y32, a.yd32, d, 0, 1.0f, dual));

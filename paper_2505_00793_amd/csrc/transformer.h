@@ -66,7 +66,7 @@ struct SoftmaxArgs {
 struct AttnArgs {
   const bf16_t *Q, *K, *V, *QT, *KT, *VT;         // per-head operands
   const bf16_t *Qd, *Kd, *Vd, *QdT, *KdT, *VdT;   // their tangents (dual)
-  bf16_t *O, *OT, *Od, *OdT;                      // token-major [N][ldO], transposed [d][ldOT]
+  bf16_t *O, *OT, *Od, *OdT;                      // token-major [N][ldO], transposed [d][ldOT] or null
   int ldO, ldOT;
   float *lse, *cst;                               // [B*H][S] saved by the forward: m + log l, <P, Sd>
   const bf16_t *dO, *dOT, *dOd, *dOdT;            // per-head cotangent of O (and its tangent)
