@@ -30,8 +30,15 @@
 // index the next product needs (lane%16), and the next product contracts over
 // the 64 keys (or queries) in a permuted order in which lane group g, element
 // t of slice c is index 16 (2c + t/4) + 4g + t%4 -- exactly the four
-// accumulator values of the lane in subtiles 2c and 2c+1.  The operand read
-// from LDS takes the same order with two 8-byte reads.
+// accumulator values of the lane in subtiles 2c and 2c+1.  The other operand of
+// that product is a transposed tile (V^T, K^T, Q^T, dO^T), read in the same order
+// from the tile's rows by two transposing LDS reads (tfrag), so every tile is
+// staged once and no transposed copies exist in memory.  The backward writes the
+// QKV product's gradient itself: dQ and dK rotated back (RoPE pairs dims j and
+// j + 32, subtiles e and e + 2 of one lane), in bf16 rows by token.
+// (With transposed tiles staged as well, six transposes a block and a merge kernel
+// between the backward and the QKV product: 4-block decoder at 16 x 256 tokens 50.8
+// -> 48.0 ms a meta-gradient, at 2 x 4096 tokens 35.4 -> 32.4 ms.)
 #include "transformer.h"
 
 namespace mfmg {
@@ -85,16 +92,23 @@ __device__ __forceinline__ void block_of(int nblk, int nbh, int& blk, int& bh) {
   blk = idx - bh * nblk;
 }
 
-// Operand fragment c of row `row` of an LDS tile in the permuted order.
-__device__ __forceinline__ bf16x8 pfrag(const bf16_t* lds, int row, int lg, int c) {
-  // elements 32c + 4 lg .. +3 and 32c + 16 + 4 lg .. +3 of the row
-  const int half = (lg & 1) * 4;
+// Operand fragment c, in the permuted order, of 16 columns e of an LDS tile: lane%16
+// is the column and the elements are rows 32c + 4 lg .. +3 and 32c + 16 + 4 lg .. +3.
+// ds_read_b64_tr_b16 works on groups of 16 lanes: lane i reads 4 elements at its own
+// address and lane j gets element j % 4 of lanes j / 4, j / 4 + 4, + 8, + 12, so with
+// lane i at row i / 4 and columns 4 (i % 4) .. + 3, lane j holds 4 rows of column j.
+// The chunk swizzle spreads the 8 rows of two lane groups over all 64 banks.
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4s lds_v4s;
+__device__ __forceinline__ bf16x8 tfrag(const bf16_t* lds, int e, int lr, int lg, int c) {
+  const int row = 32 * c + 4 * lg + (lr >> 2);
+  const bf16_t* p = lds + sw(row, 2 * e + ((lr >> 1) & 1)) + (lr & 1) * 4;
   union {
+    v4s h[2];
     bf16x8 v;
-    uint2 h[2];
   } x;
-  x.h[0] = *reinterpret_cast<const uint2*>(lds + sw(row, 4 * c + (lg >> 1)) + half);
-  x.h[1] = *reinterpret_cast<const uint2*>(lds + sw(row, 4 * c + 2 + (lg >> 1)) + half);
+  x.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
+  x.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + 16 * LP));  // row + 16
   return x.v;
 }
 
@@ -132,15 +146,15 @@ template <bool DUAL, int RB>
 __global__ void __launch_bounds__(RB * 4, RB == 64 ? (DUAL ? 2 : 3) : (DUAL ? 1 : 2))
     attn_fwd_kernel(AttnArgs a) {
   constexpr int NT = RB * 4;
-  __shared__ __attribute__((aligned(16))) bf16_t sK[AB * LP], sKd[AB * LP], sVT[DH * LP],
-      sVdT[DH * LP];
+  __shared__ __attribute__((aligned(16))) bf16_t sK[AB * LP], sKd[AB * LP], sV[AB * LP],
+      sVd[AB * LP];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
   const int S = a.S, nqb = S / RB;
   int blk, bh;
   block_of(nqb, a.BH, blk, bh);
   const int qb = nqb - 1 - blk;  // longest rows first
-  const long hb = (long)bh * S * DH, tb = (long)bh * DH * S;
+  const long hb = (long)bh * S * DH;
   const int q0 = qb * RB + w * 16;
   const int qg = q0 + lr;  // the lane's query
   bf16x8 qf[2], qdf[2];
@@ -158,10 +172,10 @@ __global__ void __launch_bounds__(RB * 4, RB == 64 ? (DUAL ? 2 : 3) : (DUAL ? 1 
   for (int kb = 0; kb < nkb; ++kb) {
     __syncthreads();
     stage<NT>(sK, a.K + hb + (long)kb * AB * DH, DH, tid);
-    stage<NT>(sVT, a.VT + tb + kb * AB, S, tid);
+    stage<NT>(sV, a.V + hb + (long)kb * AB * DH, DH, tid);
     if (DUAL) {
       stage<NT>(sKd, a.Kd + hb + (long)kb * AB * DH, DH, tid);
-      stage<NT>(sVdT, a.VdT + tb + kb * AB, S, tid);
+      stage<NT>(sVd, a.Vd + hb + (long)kb * AB * DH, DH, tid);
     }
     __syncthreads();
     f32x4 s[4], sd[4];
@@ -220,11 +234,11 @@ __global__ void __launch_bounds__(RB * 4, RB == 64 ? (DUAL ? 2 : 3) : (DUAL ? 1 
       if (DUAL) pdf = pack8(sd[2 * c], sd[2 * c + 1]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const bf16x8 vf = pfrag(sVT, e * 16 + lr, lg, c);
+        const bf16x8 vf = tfrag(sV, e, lr, lg, c);
         o[e] = mma(vf, pf, o[e]);
         if (DUAL) {
           o2[e] = mma(vf, pdf, o2[e]);
-          o3[e] = mma(pfrag(sVdT, e * 16 + lr, lg, c), pf, o3[e]);
+          o3[e] = mma(tfrag(sVd, e, lr, lg, c), pf, o3[e]);
         }
       }
     }
@@ -249,12 +263,26 @@ __global__ void __launch_bounds__(RB * 4, RB == 64 ? (DUAL ? 2 : 3) : (DUAL ? 1 
     }
     store4(a.O + tok * a.ldO + col, ov[0], ov[1], ov[2], ov[3]);
     if (DUAL) store4(a.Od + tok * a.ldO + col, odv[0], odv[1], odv[2], odv[3]);
-    if (!a.OT) continue;
+  }
+}
+
+// Rows of the QKV gradient from a lane's dims 16 e + 4 lg + r of one token: rotated
+// back by the transpose of RoPE's rotation at position pos, or (PLAIN) as they are.
+template <bool PLAIN>
+__device__ __forceinline__ void store_dqkv(bf16_t* row, const f32x4 (&g)[4], const AttnArgs& a,
+                                           int pos, int lg) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      a.OT[(long)(col + r) * a.ldOT + tok] = f2bf(ov[r]);
-      if (DUAL) a.OdT[(long)(col + r) * a.ldOT + tok] = f2bf(odv[r]);
+  for (int e = 0; e < 2; ++e) {
+    f32x4 lo = g[e], hi = g[e + 2];
+    const int j = e * 16 + 4 * lg;
+    if constexpr (!PLAIN) {
+      const f32x4 cs = *reinterpret_cast<const f32x4*>(a.cs + (long)pos * (DH / 2) + j);
+      const f32x4 sn = *reinterpret_cast<const f32x4*>(a.sn + (long)pos * (DH / 2) + j);
+      lo = g[e] * cs + sn * g[e + 2];
+      hi = g[e + 2] * cs - sn * g[e];
     }
+    store4(row + j, lo[0], lo[1], lo[2], lo[3]);
+    store4(row + 32 + j, hi[0], hi[1], hi[2], hi[3]);
   }
 }
 
@@ -264,7 +292,7 @@ __global__ void __launch_bounds__(RB * 4, RB == 64 ? (DUAL ? 2 : 3) : (DUAL ? 1 
 template <bool DUAL>
 __global__ void __launch_bounds__(256, DUAL ? 2 : 3) attn_bwd_dq_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t sK[AB * LP], sKd[AB * LP], sV[AB * LP],
-      sVd[AB * LP], sKT[DH * LP], sKdT[DH * LP];
+      sVd[AB * LP];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
   const int S = a.S, nqb = S / AB;
@@ -272,7 +300,7 @@ __global__ void __launch_bounds__(256, DUAL ? 2 : 3) attn_bwd_dq_kernel(AttnArgs
   block_of(nqb, a.BH, blk, bh);
   const int qb = nqb - 1 - blk;
   const int bs = bh / a.H, h = bh % a.H;
-  const long hb = (long)bh * S * DH, tb = (long)bh * DH * S;
+  const long hb = (long)bh * S * DH;
   const int q0 = qb * AB + w * 16;
   const int ql = w * 16 + lr;
   bf16x8 qf[2], qdf[2], gf[2], gdf[2];
@@ -312,11 +340,9 @@ __global__ void __launch_bounds__(256, DUAL ? 2 : 3) attn_bwd_dq_kernel(AttnArgs
     __syncthreads();
     stage<256>(sK, a.K + hb + (long)kb * AB * DH, DH, tid);
     stage<256>(sV, a.V + hb + (long)kb * AB * DH, DH, tid);
-    stage<256>(sKT, a.KT + tb + kb * AB, S, tid);
     if (DUAL) {
       stage<256>(sKd, a.Kd + hb + (long)kb * AB * DH, DH, tid);
       stage<256>(sVd, a.Vd + hb + (long)kb * AB * DH, DH, tid);
-      stage<256>(sKdT, a.KdT + tb + kb * AB, S, tid);
     }
     __syncthreads();
     const bool diag = kb == qb;
@@ -356,21 +382,18 @@ __global__ void __launch_bounds__(256, DUAL ? 2 : 3) attn_bwd_dq_kernel(AttnArgs
       if (DUAL) ddf = pack8(dsd[0], dsd[1]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const bf16x8 kt = pfrag(sKT, e * 16 + lr, lg, c);
+        const bf16x8 kt = tfrag(sK, e, lr, lg, c);
         dq[e] = mma(kt, df, dq[e]);
         if (DUAL) {
           dqd[e] = mma(kt, ddf, dqd[e]);
-          dqd[e] = mma(pfrag(sKdT, e * 16 + lr, lg, c), df, dqd[e]);
+          dqd[e] = mma(tfrag(sKd, e, lr, lg, c), df, dqd[e]);
         }
       }
     }
   }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const long off = hb + (long)(q0 + lr) * DH + e * 16 + 4 * lg;
-    store4(a.dQ + off, dq[e][0], dq[e][1], dq[e][2], dq[e][3]);
-    if (DUAL) store4(a.dQd + off, dqd[e][0], dqd[e][1], dqd[e][2], dqd[e][3]);
-  }
+  const long off = ((long)bs * S + q0 + lr) * a.lddqkv + h * DH;
+  store_dqkv<false>(a.dqkv + off, dq, a, q0 + lr, lg);
+  if (DUAL) store_dqkv<false>(a.dqkvd + off, dqd, a, q0 + lr, lg);
 }
 
 // ---------------------------------------------------------------- backward: dK, dV
@@ -381,14 +404,14 @@ __global__ void __launch_bounds__(256, DUAL ? 2 : 3) attn_bwd_dq_kernel(AttnArgs
 template <bool DUAL>
 __global__ void __launch_bounds__(256, 2) attn_bwd_dkv_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t sQ[AB * LP], sQd[AB * LP], sG[AB * LP],
-      sGd[AB * LP], sQT[DH * LP], sQdT[DH * LP], sGT[DH * LP], sGdT[DH * LP];
+      sGd[AB * LP];
   __shared__ __attribute__((aligned(16))) float sL[AB], sC[AB], sR[AB], sRd[AB];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
   const int S = a.S, nqb = S / AB;
   int kb, bh;  // key block 0 has the most query blocks
   block_of(nqb, a.BH, kb, bh);
-  const long hb = (long)bh * S * DH, tb = (long)bh * DH * S;
+  const long hb = (long)bh * S * DH;
   const int k0 = kb * AB + w * 16;
   const int kl = w * 16 + lr;  // the lane's key within the block
   bf16x8 kf[2], kdf[2], vf[2], vdf[2];
@@ -410,13 +433,9 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dkv_kernel(AttnArgs a) {
     __syncthreads();
     stage<256>(sQ, a.Q + hb + (long)qb * AB * DH, DH, tid);
     stage<256>(sG, a.dO + hb + (long)qb * AB * DH, DH, tid);
-    stage<256>(sQT, a.QT + tb + qb * AB, S, tid);
-    stage<256>(sGT, a.dOT + tb + qb * AB, S, tid);
     if (DUAL) {
       stage<256>(sQd, a.Qd + hb + (long)qb * AB * DH, DH, tid);
       stage<256>(sGd, a.dOd + hb + (long)qb * AB * DH, DH, tid);
-      stage<256>(sQdT, a.QdT + tb + qb * AB, S, tid);
-      stage<256>(sGdT, a.dOdT + tb + qb * AB, S, tid);
     }
     if (tid < AB) {
       const long i = (long)bh * S + qb * AB + tid;
@@ -482,27 +501,25 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dkv_kernel(AttnArgs a) {
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const bf16x8 gt = pfrag(sGT, e * 16 + lr, lg, c), qt = pfrag(sQT, e * 16 + lr, lg, c);
+        const bf16x8 gt = tfrag(sG, e, lr, lg, c), qt = tfrag(sQ, e, lr, lg, c);
         dv[e] = mma(gt, pf, dv[e]);
         dk[e] = mma(qt, df, dk[e]);
         if (DUAL) {
           dvd[e] = mma(gt, pdf, dvd[e]);
-          dvd[e] = mma(pfrag(sGdT, e * 16 + lr, lg, c), pf, dvd[e]);
+          dvd[e] = mma(tfrag(sGd, e, lr, lg, c), pf, dvd[e]);
           dkd[e] = mma(qt, ddf, dkd[e]);
-          dkd[e] = mma(pfrag(sQdT, e * 16 + lr, lg, c), df, dkd[e]);
+          dkd[e] = mma(tfrag(sQd, e, lr, lg, c), df, dkd[e]);
         }
       }
     }
   }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const long off = hb + (long)(k0 + lr) * DH + e * 16 + 4 * lg;
-    store4(a.dK + off, dk[e][0], dk[e][1], dk[e][2], dk[e][3]);
-    store4(a.dV + off, dv[e][0], dv[e][1], dv[e][2], dv[e][3]);
-    if (DUAL) {
-      store4(a.dKd + off, dkd[e][0], dkd[e][1], dkd[e][2], dkd[e][3]);
-      store4(a.dVd + off, dvd[e][0], dvd[e][1], dvd[e][2], dvd[e][3]);
-    }
+  const int d = a.H * DH;
+  const long off = ((long)(bh / a.H) * S + k0 + lr) * a.lddqkv + (bh % a.H) * DH;
+  store_dqkv<false>(a.dqkv + off + d, dk, a, k0 + lr, lg);
+  store_dqkv<true>(a.dqkv + off + 2 * d, dv, a, k0 + lr, lg);
+  if (DUAL) {
+    store_dqkv<false>(a.dqkvd + off + d, dkd, a, k0 + lr, lg);
+    store_dqkv<true>(a.dqkvd + off + 2 * d, dvd, a, k0 + lr, lg);
   }
 }
 

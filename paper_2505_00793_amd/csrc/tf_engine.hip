@@ -179,7 +179,7 @@ struct Act {  // one inner step at up to maxB sequences (the dynamic memory)
   float *cs, *sn;
 };
 
-// all: also the transposed weight-gradient operands
+// all: also the buffers that y.km and fused attention do without
 template <typename T>
 void carve_act_bufs(const Lay& y, Carver& c, Act<T>& a, bool all) {
   const long N = (long)y.maxB() * y.S, d = y.d, F = y.F, S = y.S;
@@ -188,7 +188,11 @@ void carve_act_bufs(const Lay& y, Carver& c, Act<T>& a, bool all) {
   auto F32 = [&](long n) { return c.take<float>(n); };
   auto OPT = [&](long n) { return c.take<T>(n); };
   // transposed weight-gradient operands
-  auto OPTW = [&](long n) -> T* { return all ? c.take<T>(n) : nullptr; };
+  auto OPTW = [&](long n) -> T* { return all || !y.km ? c.take<T>(n) : nullptr; };
+  // transposed and float32 per-head operands: materialised attention only
+  const bool mat = all || !y.fused;
+  auto OPTM = [&](long n) -> T* { return mat ? c.take<T>(n) : nullptr; };
+  auto F32M = [&](long n) -> float* { return mat ? c.take<float>(n) : nullptr; };
   a.ids = c.take<int>(N);
   a.labels = c.take<int>(N);
   // The residual stream: h[2b] enters block b, h[2b + 1] is its middle (after
@@ -229,12 +233,12 @@ void carve_act_bufs(const Lay& y, Carver& c, Act<T>& a, bool all) {
     a.a1d[b] = OPT(N * y.ld(d)); a.a1dT[b] = OPTW(d * y.ld(N));
     a.a2[b] = OPT(N * y.ld(d)); a.a2T[b] = OPTW(d * y.ld(N));
     a.a2d[b] = OPT(N * y.ld(d)); a.a2dT[b] = OPTW(d * y.ld(N));
-    a.Q[b] = OPT(BH * hrow); a.QT[b] = OPT(BH * hcol);
-    a.K[b] = OPT(BH * hrow); a.KT[b] = OPT(BH * hcol);
-    a.Vv[b] = OPT(BH * hrow); a.VT[b] = OPT(BH * hcol);
-    a.Qd[b] = OPT(BH * hrow); a.QdT[b] = OPT(BH * hcol);
-    a.Kd[b] = OPT(BH * hrow); a.KdT[b] = OPT(BH * hcol);
-    a.Vd[b] = OPT(BH * hrow); a.VdT[b] = OPT(BH * hcol);
+    a.Q[b] = OPT(BH * hrow); a.QT[b] = OPTM(BH * hcol);
+    a.K[b] = OPT(BH * hrow); a.KT[b] = OPTM(BH * hcol);
+    a.Vv[b] = OPT(BH * hrow); a.VT[b] = OPTM(BH * hcol);
+    a.Qd[b] = OPT(BH * hrow); a.QdT[b] = OPTM(BH * hcol);
+    a.Kd[b] = OPT(BH * hrow); a.KdT[b] = OPTM(BH * hcol);
+    a.Vd[b] = OPT(BH * hrow); a.VdT[b] = OPTM(BH * hcol);
     if (y.fused) {
       a.P32[b] = a.Pd32[b] = nullptr;
       a.Pb[b] = a.PbT[b] = a.Pdb[b] = a.PdbT[b] = nullptr;
@@ -257,8 +261,8 @@ void carve_act_bufs(const Lay& y, Carver& c, Act<T>& a, bool all) {
   a.logits = F32(N * y.V); a.logitsd = F32(N * y.V);
   a.y32 = F32(N * std::max(d, F)); a.yd32 = F32(N * std::max(d, F));
   a.qkv32 = F32(N * 3 * d); a.qkvd32 = F32(N * 3 * d);
-  a.Qh = F32(N * d); a.Kh = F32(N * d); a.Vh = F32(N * d);
-  a.Qdh = F32(N * d); a.Kdh = F32(N * d); a.Vdh = F32(N * d);
+  a.Qh = F32M(N * d); a.Kh = F32M(N * d); a.Vh = F32M(N * d);
+  a.Qdh = F32M(N * d); a.Kdh = F32M(N * d); a.Vdh = F32M(N * d);
   if (y.fused) {
     a.S32 = a.Sd32 = a.dS32 = a.dSd32 = nullptr;
     a.dS = a.dST = a.dSd = a.dSdT = nullptr;
@@ -278,8 +282,8 @@ void carve_act_bufs(const Lay& y, Carver& c, Act<T>& a, bool all) {
   const long FQ = std::max(F, 3 * d);  // also holds the dqkv operands
   a.dZ1 = OPT(N * y.ld(FQ)); a.dZ1T = OPTW(FQ * y.ld(N));
   a.dZ1d = OPT(N * y.ld(FQ)); a.dZ1dT = OPTW(FQ * y.ld(N));
-  a.dOh = OPT(BH * hrow); a.dOhT = OPT(BH * hcol);
-  a.dOdh = OPT(BH * hrow); a.dOdhT = OPT(BH * hcol);
+  a.dOh = OPT(BH * hrow); a.dOhT = OPTM(BH * hcol);
+  a.dOdh = OPT(BH * hrow); a.dOdhT = OPTM(BH * hcol);
   a.lnpart = F32((long)ln_bwd_parts((int)N) * 4 * d);
   const long nsm = embed_segments_max((int)N);
   a.ts = carve_segs(c, N, y.V);
@@ -300,7 +304,7 @@ void carve_act(const Lay& y, Carver& c, Act<T>& a) {
   Carver size{nullptr, c.off};
   Act<T> none;
   carve_act_bufs(y, size, none, true);
-  carve_act_bufs(y, c, a, !y.km);
+  carve_act_bufs(y, c, a, false);
   c.off = size.off;
 }
 
@@ -418,26 +422,32 @@ struct TfEng {
                                 (int)y.ld(N), in, out, N), a),
                          fl(dual), P, s);
   }
+  // Transposed copies (where the plan has them) of weight-gradient operand rows
+  // [N][ld(cols)], N a multiple of 8.
+  hipError_t wgrad_copy(const T* x, const T* xd, int N, int cols, T* xT, T* xdT) const {
+    if constexpr (std::is_same<T, bf16_t>::value)
+      if (!y.km)
+        return transpose_bf16(x, xd, N, cols, (int)y.ld(cols), xT, xd ? xdT : nullptr,
+                              (int)y.ld(N), s);
+    return hipSuccess;
+  }
   // Operands of block b's fused attention (bf16 only: the option is rejected
   // for float32 operands before any plan is made).
   AttnArgs attn_args(int b, int Bn, bool dual, const Act<T>& a) const {
     AttnArgs t;
     std::memset(&t, 0, sizeof(t));
     if constexpr (std::is_same<T, bf16_t>::value) {
-      t.Q = a.Q[b]; t.K = a.K[b]; t.V = a.Vv[b]; t.QT = a.QT[b]; t.KT = a.KT[b]; t.VT = a.VT[b];
+      t.Q = a.Q[b]; t.K = a.K[b]; t.V = a.Vv[b];
+      t.O = a.O[b]; t.dO = a.dOh; t.dqkv = a.dZ1;
       if (dual) {
         t.Qd = a.Qd[b]; t.Kd = a.Kd[b]; t.Vd = a.Vd[b];
-        t.QdT = a.QdT[b]; t.KdT = a.KdT[b]; t.VdT = a.VdT[b];
+        t.Od = a.Od[b]; t.dOd = a.dOdh; t.dqkvd = a.dZ1d;
       }
-      t.O = a.O[b]; t.OT = a.OT[b];
-      t.Od = dual ? a.Od[b] : nullptr; t.OdT = dual ? a.OdT[b] : nullptr;
-      t.dO = a.dOh; t.dOT = a.dOhT;
-      t.dOd = dual ? a.dOdh : nullptr; t.dOdT = dual ? a.dOdhT : nullptr;
     }
     t.ldO = (int)y.ld(y.d);
-    t.ldOT = (int)y.ld((long)Bn * y.S);
+    t.lddqkv = (int)y.ld(3 * y.d);
     t.lse = a.lse[b]; t.cst = a.cst[b]; t.r = a.ar; t.rd = a.ard;
-    t.dQ = a.Qh; t.dK = a.Kh; t.dV = a.Vh; t.dQd = a.Qdh; t.dKd = a.Kdh; t.dVd = a.Vdh;
+    t.cs = a.cs; t.sn = a.sn;
     t.S = y.S; t.H = y.H; t.BH = Bn * y.H; t.dh = y.dh; t.dual = dual;
     t.scale = 1.0f / std::sqrt((float)y.dh);
     return t;
@@ -479,9 +489,7 @@ struct TfEng {
       if (ln_direct(ln.N)) {
         ln.yb = row; ln.ydb = dual ? rowd : nullptr; ln.ldb = (int)y.ld(y.d);
         HC(ln_fwd(ln, s));
-        if (y.km) return hipSuccess;
-        return transpose_bf16(row, dual ? rowd : nullptr, ln.N, y.d, (int)y.ld(y.d), tr,
-                              dual ? trd : nullptr, (int)y.ld(ln.N), s);
+        return wgrad_copy(row, dual ? rowd : nullptr, ln.N, y.d, tr, trd);
       }
     }
     HC(ln_fwd(ln, s));
@@ -491,10 +499,7 @@ struct TfEng {
   // after the LayerNorm backward that produced it.
   hipError_t dh_operands(int N, bool dual, const Act<T>& a) const {
     if constexpr (std::is_same<T, bf16_t>::value) {
-      if (ln_direct(N) && y.km) return hipSuccess;
-      if (ln_direct(N))
-        return transpose_bf16(a.dhb, dual ? a.dhdb : nullptr, N, y.d, (int)y.ld(y.d), a.dhbT,
-                              dual ? a.dhdbT : nullptr, (int)y.ld(N), s);
+      if (ln_direct(N)) return wgrad_copy(a.dhb, dual ? a.dhdb : nullptr, N, y.d, a.dhbT, a.dhdbT);
     }
     return convs({{a.dh, a.dhb, a.dhbT}, {dual ? a.dhd : nullptr, a.dhdb, a.dhdbT}}, N, y.d);
   }
@@ -630,7 +635,9 @@ struct TfEng {
       }
       HC(rope_split(r, s));
       const long sh = (long)S * dh;
-      if (qdirect) {
+      if (y.fused) {
+        // bf16 rows (S is a multiple of 64) are all it reads
+      } else if (qdirect) {
         if constexpr (std::is_same<T, bf16_t>::value) {
           TrJobs J;
           auto add = [&](const bf16_t* src, bf16_t* dst) {
@@ -649,6 +656,7 @@ struct TfEng {
       }
       if (y.fused) {
         HC(attn_fwd(attn_args(b, Bn, dual, a), s));
+        HC(wgrad_copy(a.O[b], dual ? a.Od[b] : nullptr, N, d, a.OT[b], a.OdT[b]));
       } else {
         // scores S = scale Q K^T (per head), softmax
         {
@@ -815,6 +823,7 @@ struct TfEng {
       }
       if (y.fused) {
         HC(attn_bwd(attn_args(b, Bn, dual, a), s));
+        HC(wgrad_copy(a.dZ1, dual ? a.dZ1d : nullptr, N, 3 * d, a.dZ1T, a.dZ1dT));
       } else {
         {  // dP = dO V^T
           GemmOperands<T> o = op(a.dOh, dual ? a.dOdh : nullptr, a.Vv[b], dual ? a.Vd[b] : nullptr,
@@ -848,29 +857,27 @@ struct TfEng {
           o.batch = BH; o.sA = pS; o.sB = hcol;
           HC(store(o, fl(dual), a.Kh, a.Kdh, dh, (long)S * dh, 1.0f, dual));
         }
-      }
-      RopeArgs r;
-      std::memset(&r, 0, sizeof(r));
-      r.Q = a.Qh; r.K = a.Kh; r.V = a.Vh; r.Qd = a.Qdh; r.Kd = a.Kdh; r.Vd = a.Vdh;
-      r.qkv_out = a.qkv32; r.qkvd_out = a.qkvd32;
-      r.cs = a.cs; r.sn = a.sn; r.N = N; r.S = S; r.H = H; r.dh = dh; r.dual = dual;
-      // dqkv operands in the dZ1 buffers (sized for max(F, 3d)): bf16 rows
-      // straight from the merge and a bf16 transpose, or float32 rows converted
-      bool direct = false;
-      if constexpr (std::is_same<T, bf16_t>::value) {
-        if (N % 8 == 0) {
-          direct = true;
-          r.ob = a.dZ1; r.odb = dual ? a.dZ1d : nullptr; r.ldb = (int)y.ld(3 * d);
+        RopeArgs r;
+        std::memset(&r, 0, sizeof(r));
+        r.Q = a.Qh; r.K = a.Kh; r.V = a.Vh; r.Qd = a.Qdh; r.Kd = a.Kdh; r.Vd = a.Vdh;
+        r.qkv_out = a.qkv32; r.qkvd_out = a.qkvd32;
+        r.cs = a.cs; r.sn = a.sn; r.N = N; r.S = S; r.H = H; r.dh = dh; r.dual = dual;
+        // dqkv operands in the dZ1 buffers (sized for max(F, 3d)): bf16 rows
+        // straight from the merge and a bf16 transpose, or float32 rows converted
+        bool direct = false;
+        if constexpr (std::is_same<T, bf16_t>::value) {
+          if (N % 8 == 0) {
+            direct = true;
+            r.ob = a.dZ1; r.odb = dual ? a.dZ1d : nullptr; r.ldb = (int)y.ld(3 * d);
+          }
         }
-      }
-      HC(rope_merge(r, s));
-      if (direct) {
-        if constexpr (std::is_same<T, bf16_t>::value) if (!y.km)
-          HC(transpose_bf16(a.dZ1, dual ? a.dZ1d : nullptr, N, 3 * d, (int)y.ld(3 * d), a.dZ1T,
-                            dual ? a.dZ1dT : nullptr, (int)y.ld(N), s));
-      } else {
-        HC(convs({{a.qkv32, a.dZ1, a.dZ1T}, {dual ? a.qkvd32 : nullptr, a.dZ1d, a.dZ1dT}}, N,
-                 3 * d));
+        HC(rope_merge(r, s));
+        if (direct) {
+          HC(wgrad_copy(a.dZ1, dual ? a.dZ1d : nullptr, N, 3 * d, a.dZ1T, a.dZ1dT));
+        } else {
+          HC(convs({{a.qkv32, a.dZ1, a.dZ1T}, {dual ? a.qkvd32 : nullptr, a.dZ1d, a.dZ1dT}}, N,
+                   3 * d));
+        }
       }
       HC(wgrad(a.a1[b], a.a1d[b], a.a1T[b], a.a1dT[b], a.dZ1, a.dZ1d, a.dZ1T, a.dZ1dT, d, 3 * d, N,
                dual,

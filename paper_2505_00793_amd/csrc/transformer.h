@@ -61,17 +61,19 @@ struct SoftmaxArgs {
 };
 
 // Fused causal attention of head dimension 64 over bf16 operands (forward and
-// backward, primal or dual).  Per-head operands are rows [B*H][S][64] and
-// transposes [B*H][64][S]; S is a multiple of 64.
+// backward, primal or dual).  Per-head operands are rows [B*H][S][64]; S is a
+// multiple of 64.
 struct AttnArgs {
-  const bf16_t *Q, *K, *V, *QT, *KT, *VT;         // per-head operands
-  const bf16_t *Qd, *Kd, *Vd, *QdT, *KdT, *VdT;   // their tangents (dual)
-  bf16_t *O, *OT, *Od, *OdT;                      // token-major [N][ldO], transposed [d][ldOT] or null
-  int ldO, ldOT;
+  const bf16_t *Q, *K, *V;                        // per-head operands (Q, K rotated)
+  const bf16_t *Qd, *Kd, *Vd;                     // their tangents (dual)
+  bf16_t *O, *Od;                                 // token-major [N][ldO]
+  int ldO;
   float *lse, *cst;                               // [B*H][S] saved by the forward: m + log l, <P, Sd>
-  const bf16_t *dO, *dOT, *dOd, *dOdT;            // per-head cotangent of O (and its tangent)
+  const bf16_t *dO, *dOd;                         // per-head cotangent of O (and its tangent)
   float *r, *rd;                                  // [B*H][S] <dO, O>, <dOd, O> + <dO, Od>
-  float *dQ, *dK, *dV, *dQd, *dKd, *dVd;          // fp32 per-head rows [B*H][S][64]
+  bf16_t *dqkv, *dqkvd;                           // gradient of the QKV product (before RoPE), token-
+  int lddqkv;                                     //   major rows [N][lddqkv]: q | k | v heads
+  const float *cs, *sn;                           // RoPE table [S][32]
   int S, H, BH, dh, dual;
   float scale;
 };
