@@ -73,6 +73,26 @@ __device__ __forceinline__ void stage(bf16_t* lds, const bf16_t* __restrict__ g,
   }
 }
 
+// The same on its way through registers: the next block's tiles are requested
+// before the current block's products and stored to the other LDS buffer after
+// them, with one barrier a block instead of two around the latency of the loads
+// (S = 4096, 16 heads: dual forward 233 -> 163 us, dual dK/dV 272 -> 235 us, primal
+// forward 95 -> 93 us, primal dK/dV 136 -> 126 us).  The dual dQ pass was slower so
+// (182 -> 195 us) and stages straight into one buffer.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+template <int NT>
+struct TileRegs {
+  u32x4 u, v;
+  __device__ __forceinline__ void load(const bf16_t* __restrict__ g, int tid) {
+    u = *reinterpret_cast<const u32x4*>(g + tid * 8);
+    if constexpr (NT == 256) v = *reinterpret_cast<const u32x4*>(g + (tid + 256) * 8);
+  }
+  __device__ __forceinline__ void store(bf16_t* lds, int tid) const {
+    *reinterpret_cast<u32x4*>(lds + sw(tid >> 3, tid & 7)) = u;
+    if constexpr (NT == 256) *reinterpret_cast<u32x4*>(lds + sw((tid >> 3) + 32, tid & 7)) = v;
+  }
+};
+
 // Operand fragment c (0, 1) of row `row` of an LDS tile.
 __device__ __forceinline__ bf16x8 frag(const bf16_t* lds, int row, int lg, int c) {
   return ld8(lds + sw(row, lg + 4 * c));
@@ -146,8 +166,8 @@ template <bool DUAL, int RB>
 __global__ void __launch_bounds__(RB * 4, RB == 64 ? (DUAL ? 2 : 3) : (DUAL ? 1 : 2))
     attn_fwd_kernel(AttnArgs a) {
   constexpr int NT = RB * 4;
-  __shared__ __attribute__((aligned(16))) bf16_t sK[AB * LP], sKd[AB * LP], sV[AB * LP],
-      sVd[AB * LP];
+  __shared__ __attribute__((aligned(16))) bf16_t bK[2][AB * LP], bKd[2][AB * LP], bV[2][AB * LP],
+      bVd[2][AB * LP];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
   const int S = a.S, nqb = S / RB;
@@ -169,15 +189,30 @@ __global__ void __launch_bounds__(RB * 4, RB == 64 ? (DUAL ? 2 : 3) : (DUAL ? 1 
   for (int i = 0; i < 4; ++i) { o[i] = zero4(); o2[i] = zero4(); o3[i] = zero4(); }
   const float sc = a.scale;
   const int nkb = (qb + 1) * RB / AB;
-  for (int kb = 0; kb < nkb; ++kb) {
-    __syncthreads();
-    stage<NT>(sK, a.K + hb + (long)kb * AB * DH, DH, tid);
-    stage<NT>(sV, a.V + hb + (long)kb * AB * DH, DH, tid);
+  TileRegs<NT> rK, rKd, rV, rVd;
+  auto load = [&](int kb) {
+    const long o = hb + (long)kb * AB * DH;
+    rK.load(a.K + o, tid);
+    rV.load(a.V + o, tid);
     if (DUAL) {
-      stage<NT>(sKd, a.Kd + hb + (long)kb * AB * DH, DH, tid);
-      stage<NT>(sVd, a.Vd + hb + (long)kb * AB * DH, DH, tid);
+      rKd.load(a.Kd + o, tid);
+      rVd.load(a.Vd + o, tid);
     }
-    __syncthreads();
+  };
+  auto store = [&](int buf) {
+    rK.store(bK[buf], tid);
+    rV.store(bV[buf], tid);
+    if (DUAL) {
+      rKd.store(bKd[buf], tid);
+      rVd.store(bVd[buf], tid);
+    }
+  };
+  load(0);
+  store(0);
+  for (int kb = 0; kb < nkb; ++kb) {
+    __syncthreads();   // block kb is in its buffer, and nobody reads the other one
+    load(min(kb + 1, nkb - 1));   // (the last block's again at the end, into a dead buffer)
+    const bf16_t *sK = bK[kb & 1], *sKd = bKd[kb & 1], *sV = bV[kb & 1], *sVd = bVd[kb & 1];
     f32x4 s[4], sd[4];
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
@@ -242,6 +277,7 @@ __global__ void __launch_bounds__(RB * 4, RB == 64 ? (DUAL ? 2 : 3) : (DUAL ? 1 
         }
       }
     }
+    store((kb + 1) & 1);
   }
   const int bs = bh / a.H, h = bh % a.H;
   const long tok = (long)bs * S + q0 + lr;
@@ -403,9 +439,9 @@ __global__ void __launch_bounds__(256, DUAL ? 2 : 3) attn_bwd_dq_kernel(AttnArgs
 // dV^T += dO^T P and dK^T += Q^T dS.
 template <bool DUAL>
 __global__ void __launch_bounds__(256, 2) attn_bwd_dkv_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16_t sQ[AB * LP], sQd[AB * LP], sG[AB * LP],
-      sGd[AB * LP];
-  __shared__ __attribute__((aligned(16))) float sL[AB], sC[AB], sR[AB], sRd[AB];
+  __shared__ __attribute__((aligned(16))) bf16_t bQ[2][AB * LP], bQd[2][AB * LP], bG[2][AB * LP],
+      bGd[2][AB * LP];
+  __shared__ __attribute__((aligned(16))) float bL[2][AB], bC[2][AB], bR[2][AB], bRd[2][AB];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
   const int S = a.S, nqb = S / AB;
@@ -429,24 +465,47 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dkv_kernel(AttnArgs a) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) { dk[e] = zero4(); dkd[e] = zero4(); dv[e] = zero4(); dvd[e] = zero4(); }
   const float sc = a.scale;
-  for (int qb = kb; qb < nqb; ++qb) {
-    __syncthreads();
-    stage<256>(sQ, a.Q + hb + (long)qb * AB * DH, DH, tid);
-    stage<256>(sG, a.dO + hb + (long)qb * AB * DH, DH, tid);
+  TileRegs<256> rQ, rQd, rG, rGd;
+  float xL = 0.f, xC = 0.f, xR = 0.f, xRd = 0.f;   // a query's row values (threads 0..63)
+  auto load = [&](int qb) {
+    const long o = hb + (long)qb * AB * DH;
+    rQ.load(a.Q + o, tid);
+    rG.load(a.dO + o, tid);
     if (DUAL) {
-      stage<256>(sQd, a.Qd + hb + (long)qb * AB * DH, DH, tid);
-      stage<256>(sGd, a.dOd + hb + (long)qb * AB * DH, DH, tid);
+      rQd.load(a.Qd + o, tid);
+      rGd.load(a.dOd + o, tid);
+    }
+    const long i = (long)bh * S + qb * AB + (tid & 63);
+    xL = a.lse[i];
+    xR = a.r[i];
+    if (DUAL) {
+      xC = a.cst[i];
+      xRd = a.rd[i];
+    }
+  };
+  auto store = [&](int buf) {
+    rQ.store(bQ[buf], tid);
+    rG.store(bG[buf], tid);
+    if (DUAL) {
+      rQd.store(bQd[buf], tid);
+      rGd.store(bGd[buf], tid);
     }
     if (tid < AB) {
-      const long i = (long)bh * S + qb * AB + tid;
-      sL[tid] = a.lse[i];
-      sR[tid] = a.r[i];
+      bL[buf][tid] = xL;
+      bR[buf][tid] = xR;
       if (DUAL) {
-        sC[tid] = a.cst[i];
-        sRd[tid] = a.rd[i];
+        bC[buf][tid] = xC;
+        bRd[buf][tid] = xRd;
       }
     }
+  };
+  load(kb);
+  store(kb & 1);
+  for (int qb = kb; qb < nqb; ++qb) {
     __syncthreads();
+    load(min(qb + 1, nqb - 1));
+    const bf16_t *sQ = bQ[qb & 1], *sQd = bQd[qb & 1], *sG = bG[qb & 1], *sGd = bGd[qb & 1];
+    const float *sL = bL[qb & 1], *sC = bC[qb & 1], *sR = bR[qb & 1], *sRd = bRd[qb & 1];
     const bool diag = kb == qb;
     // Slice c of the query contraction: subtiles 2c, 2c+1 are formed, packed
     // and consumed before the next pair, which keeps half as many values live.
@@ -512,6 +571,7 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dkv_kernel(AttnArgs a) {
         }
       }
     }
+    store((qb + 1) & 1);
   }
   const int d = a.H * DH;
   const long off = ((long)(bh / a.H) * S + k0 + lr) * a.lddqkv + (bh % a.H) * DH;
