@@ -410,6 +410,37 @@ struct ParamOp {
   }
 };
 
+// QKV product of fused attention: columns q heads | k heads | v heads of 64 dims;
+// q and k are rotated (RoPE pairs dims j and j + 32 of a head, both in the tile) and
+// every head's rows stored in bf16.
+struct QkvRopeOp {
+  EpiQkvRope e;
+  int M, N;
+  static constexpr bool PRELOAD = false;
+  typedef int In;
+  __device__ int n_trans() const { return 0; }
+  // cos and sin of the rotation of columns n .. n + 3 of row m (sign: -sin for the
+  // lower half of a head); v columns read a rotation they do not use
+  __device__ __forceinline__ void angles(int m, int n, f32x4& cs, f32x4& sn) const {
+    const long o = (long)(m % e.S) * 32 + (n & 31);
+    cs = *reinterpret_cast<const f32x4*>(e.cs + o);
+    sn = *reinterpret_cast<const f32x4*>(e.sn + o);
+    if (!(n & 32)) sn = -sn;
+  }
+  // columns n .. n + 3 of row m from its values x and their partners' y
+  __device__ __forceinline__ void put(bf16_t* Q, bf16_t* K, bf16_t* V, int m, int n,
+                                      const f32x4& x, const f32x4& y, const f32x4& cs,
+                                      const f32x4& sn) const {
+    const int d = e.H * 64, sec = n / d, h = (n - sec * d) >> 6;
+    const int b = m / e.S;
+    const long off = ((long)(b * e.H + h) * e.S + (m - b * e.S)) * 64 + (n & 63);
+    const f32x4 v = sec == 2 ? x : x * cs + sn * y;
+    store4((sec == 0 ? Q : sec == 1 ? K : V) + off, v[0], v[1], v[2], v[3]);
+  }
+};
+template <class E> struct IsQkvRopeOp : std::false_type {};
+template <> struct IsQkvRopeOp<QkvRopeOp> : std::true_type {};
+
 // Epilogues whose operand outputs may have padding to clear (see zero_tile_pads).
 template <class E> struct HasPads : std::false_type {};
 template <typename T> struct HasPads<ActFwdOp<T>> : std::true_type {};
@@ -670,6 +701,29 @@ __device__ __forceinline__ void walk_tile(float* S1, float* S2, int mr0, int n0,
   constexpr bool HC2 = (FLAGS & (G_AD | G_BD)) != 0;
   constexpr int SLD = Stage<BN>::SLD;
   const int tid = threadIdx.x;
+  if constexpr (IsQkvRopeOp<Epi>::value) {
+    // a thread's rotation factors requested together, then its rows
+    constexpr int TPR = BN / 4, RPI = NT / TPR, NIT = RP / RPI;
+    static_assert(BN % 64 == 0 && RP % RPI == 0, "whole heads");
+    const int c = (tid % TPR) * 4, n = n0 + c;
+    f32x4 cs[NIT], sn[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it)
+      epi.angles(min(mr0 + tid / TPR + it * RPI, epi.M - 1), n, cs[it], sn[it]);
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const int rr = tid / TPR + it * RPI, m = mr0 + rr;
+      if (m < epi.M && n < epi.N) {
+        const int si = stage_idx<SLD>(rr, c), sp = stage_idx<SLD>(rr, c ^ 32);
+        epi.put(epi.e.Q, epi.e.K, epi.e.V, m, n, *reinterpret_cast<const f32x4*>(S1 + si),
+                *reinterpret_cast<const f32x4*>(S1 + sp), cs[it], sn[it]);
+        if constexpr (HC2)
+          epi.put(epi.e.Qd, epi.e.Kd, epi.e.Vd, m, n, *reinterpret_cast<const f32x4*>(S2 + si),
+                  *reinterpret_cast<const f32x4*>(S2 + sp), cs[it], sn[it]);
+      }
+    }
+    __syncthreads();
+  } else {
   const int nT = epi.n_trans();
   bool walked = false;
   if constexpr (Epi::PRELOAD && NT == 512) {
@@ -786,6 +840,7 @@ __device__ __forceinline__ void walk_tile(float* S1, float* S2, int mr0, int n0,
   }
   if constexpr (HasPads<Epi>::value) epi.pads(mr0, RP, n0, BN);
   __syncthreads();
+  }
 }
 
 // Epilogue of the 256-thread kernels.  A 64-row tile is staged whole (it fits in
@@ -1864,6 +1919,35 @@ hipError_t gemm_param(const GemmOperands<T>& op, int flags, const ParamArgs<T>& 
 }
 
 #if !defined(GEMM_PART) || GEMM_PART == 8
+namespace {
+// Tiles of whole 64-wide heads: 128 x 128 or 128 x 64 where these fill the chip (as
+// in launch_sized), else 64 x 64.
+template <int FLAGS>
+hipError_t launch_qkv(const GemmOperands<bf16_t>& op, const QkvRopeOp& epi, hipStream_t s) {
+  auto go = [&](auto kernel, int bm, int bn) {
+    hipLaunchKernelGGL(kernel, dim3(cdiv(op.M, bm) * cdiv(op.N, bn)), dim3(512), 0, s, op, epi);
+    return hipGetLastError();
+  };
+  constexpr int NST = DmaShape<bf16_t, FLAGS>::NST;
+  if (cdiv(op.M, 128) * cdiv(op.N, 128) >= 192)
+    return go(gemm_nt_ws<bf16_t, FLAGS, 128, 128, NST, QkvRopeOp>, 128, 128);
+  if (cdiv(op.M, 128) * cdiv(op.N, 64) >= 192)
+    return go(gemm_nt_ws<bf16_t, FLAGS, 128, 64, NST, QkvRopeOp>, 128, 64);
+  constexpr int NST64 = DmaDepth<bf16_t, FLAGS, 64, 64, 147456>::NST;
+  return go(gemm_nt_ws<bf16_t, FLAGS, 64, 64, NST64, QkvRopeOp>, 64, 64);
+}
+}  // namespace
+
+hipError_t gemm_qkv_rope(const GemmOperands<bf16_t>& op, int flags, const EpiQkvRope& e,
+                         hipStream_t s) {
+  if (op.batch != 1 || op.M <= 0 || op.N != 3 * 64 * e.H || e.S < 1 || op.M % e.S || !dma_ok(op))
+    return hipErrorInvalidValue;
+  const QkvRopeOp epi{e, op.M, op.N};
+  if (flags == G_C1) return launch_qkv<G_C1>(op, epi, s);
+  if (flags == (G_C1 | G_AD | G_BD)) return launch_qkv<G_C1 | G_AD | G_BD>(op, epi, s);
+  return hipErrorInvalidValue;
+}
+
 hipError_t gemm_param_km(const GemmOperands<bf16_t>& op, int flags, const ParamArgs<bf16_t>& P,
                          hipStream_t s) {
   if (op.batch != 1 || P.b_off >= 0 || !km_ok(op)) return hipErrorInvalidValue;

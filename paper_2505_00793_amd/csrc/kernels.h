@@ -131,6 +131,16 @@ struct EpiHeadSplit {
   int M, N, dual;
 };
 
+// The QKV product of fused attention ([tokens][3 d], d = 64 H, tokens = sequences of
+// S): q and k rotated by RoPE at the token's position, stored with v as per-head
+// bf16 rows [B * H][S][64].
+struct EpiQkvRope {
+  bf16_t *Q, *K, *V;
+  bf16_t *Qd, *Kd, *Vd;    // tangents (dual)
+  const float *cs, *sn;    // RoPE table [S][32]
+  int S, H;
+};
+
 enum ParamMode {
   P_UPD_SGD_PP = 0,     // theta' = theta - exp(eta) g
   P_UPD_SGD_FIXED = 1,  // theta' = theta - lr g
@@ -207,7 +217,9 @@ hipError_t gemm_act_bwd(const GemmOperands<T>& op, int flags, const EpiActBwd<T>
 template <typename T>
 hipError_t gemm_param(const GemmOperands<T>& op, int flags, const ParamArgs<T>& P,
                       hipStream_t s);
-// The same for operands stored with the contraction index outermost: C1 = A^T B
+hipError_t gemm_qkv_rope(const GemmOperands<bf16_t>& op, int flags, const EpiQkvRope& e,
+                         hipStream_t s);
+// Weight gradients of operands stored with the contraction index outermost: C1 = A^T B
 // of A [K][lda], B [K][ldb] (and their tangents), for matrices without a bias
 // (P.b_off < 0); 16-byte aligned, leading dimensions multiples of 8, each operand
 // under 2 GB, any K.

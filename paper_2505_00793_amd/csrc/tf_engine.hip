@@ -622,45 +622,57 @@ struct TfEng {
       ln.y = a.y32; ln.yd = a.yd32; ln.xh = a.xh1[b]; ln.xhd = a.xhd1[b];
       ln.rstd = a.rs1[b]; ln.c = a.c1[b]; ln.N = N; ln.d = d; ln.dual = dual; ln.eps = y.eps;
       HC(ln_operands(ln, a.a1[b], a.a1d[b], a.a1T[b], a.a1dT[b]));
-      // qkv = a1 Wqkv
-      HC(store(op(a.a1[b], dual ? a.a1d[b] : nullptr, th.WT[b][0], dual ? v->WT[b][0] : nullptr,
-                  (int)y.ld(d), (int)y.ld(d), N, 3 * d, d),
-               fl(dual), a.qkv32, a.qkvd32, 3 * d, 0, 1.0f, dual));
-      RopeArgs r;
-      std::memset(&r, 0, sizeof(r));
-      r.qkv = a.qkv32; r.qkvd = a.qkvd32;
-      r.Q = a.Qh; r.K = a.Kh; r.V = a.Vh; r.Qd = a.Qdh; r.Kd = a.Kdh; r.Vd = a.Vdh;
-      r.cs = a.cs; r.sn = a.sn; r.N = N; r.S = S; r.H = H; r.dh = dh; r.dual = dual;
-      // per-head operands: bf16 rows straight from the split and batched bf16
-      // transposes (S a multiple of 8), or float32 per-head rows converted
-      bool qdirect = false;
-      if constexpr (std::is_same<T, bf16_t>::value) {
-        if (S % 8 == 0) {
-          qdirect = true;
-          r.Qb = a.Q[b]; r.Kb = a.K[b]; r.Vb = a.Vv[b];
-          if (dual) { r.Qdb = a.Qd[b]; r.Kdb = a.Kd[b]; r.Vdb = a.Vd[b]; }
-        }
-      }
-      HC(rope_split(r, s));
-      const long sh = (long)S * dh;
+      // qkv = a1 Wqkv, rotated by RoPE, per head
       if (y.fused) {
-        // bf16 rows (S is a multiple of 64) are all it reads
-      } else if (qdirect) {
         if constexpr (std::is_same<T, bf16_t>::value) {
-          TrJobs J;
-          auto add = [&](const bf16_t* src, bf16_t* dst) {
-            J.src[J.n] = src; J.dst[J.n] = dst; ++J.n;
-          };
-          add(a.Q[b], a.QT[b]); add(a.K[b], a.KT[b]); add(a.Vv[b], a.VT[b]);
-          if (dual) { add(a.Qd[b], a.QdT[b]); add(a.Kd[b], a.KdT[b]); add(a.Vd[b], a.VdT[b]); }
-          HC(transpose_bf16_jobs(J, BH, S, dh, (int)y.ld(dh), (int)y.ld(S), hrow, hcol, s));
+          // straight from the product's epilogue (4096 tokens, d 512, dual: 39.7 us; the
+          // float32 product and a split kernel took 38.8 + 12.4 us)
+          EpiQkvRope e;
+          e.Q = a.Q[b]; e.K = a.K[b]; e.V = a.Vv[b];
+          e.Qd = a.Qd[b]; e.Kd = a.Kd[b]; e.Vd = a.Vd[b];
+          e.cs = a.cs; e.sn = a.sn; e.S = S; e.H = H;
+          HC(gemm_qkv_rope(op(a.a1[b], dual ? a.a1d[b] : nullptr, th.WT[b][0],
+                              dual ? v->WT[b][0] : nullptr, (int)y.ld(d), (int)y.ld(d), N, 3 * d, d),
+                           fl(dual), e, s));
         }
       } else {
-        HC(convs({{a.Qh, a.Q[b], a.QT[b]}, {a.Kh, a.K[b], a.KT[b]}, {a.Vh, a.Vv[b], a.VT[b]},
-                  {dual ? a.Qdh : nullptr, a.Qd[b], a.QdT[b]},
-                  {dual ? a.Kdh : nullptr, a.Kd[b], a.KdT[b]},
-                  {dual ? a.Vdh : nullptr, a.Vd[b], a.VdT[b]}},
-                 S, dh, BH, sh, hrow, hcol));
+        HC(store(op(a.a1[b], dual ? a.a1d[b] : nullptr, th.WT[b][0], dual ? v->WT[b][0] : nullptr,
+                    (int)y.ld(d), (int)y.ld(d), N, 3 * d, d),
+                 fl(dual), a.qkv32, a.qkvd32, 3 * d, 0, 1.0f, dual));
+        RopeArgs r;
+        std::memset(&r, 0, sizeof(r));
+        r.qkv = a.qkv32; r.qkvd = a.qkvd32;
+        r.Q = a.Qh; r.K = a.Kh; r.V = a.Vh; r.Qd = a.Qdh; r.Kd = a.Kdh; r.Vd = a.Vdh;
+        r.cs = a.cs; r.sn = a.sn; r.N = N; r.S = S; r.H = H; r.dh = dh; r.dual = dual;
+        // per-head operands: bf16 rows straight from the split and batched bf16
+        // transposes (S a multiple of 8), or float32 per-head rows converted
+        bool qdirect = false;
+        if constexpr (std::is_same<T, bf16_t>::value) {
+          if (S % 8 == 0) {
+            qdirect = true;
+            r.Qb = a.Q[b]; r.Kb = a.K[b]; r.Vb = a.Vv[b];
+            if (dual) { r.Qdb = a.Qd[b]; r.Kdb = a.Kd[b]; r.Vdb = a.Vd[b]; }
+          }
+        }
+        HC(rope_split(r, s));
+        const long sh = (long)S * dh;
+        if (qdirect) {
+          if constexpr (std::is_same<T, bf16_t>::value) {
+            TrJobs J;
+            auto add = [&](const bf16_t* src, bf16_t* dst) {
+              J.src[J.n] = src; J.dst[J.n] = dst; ++J.n;
+            };
+            add(a.Q[b], a.QT[b]); add(a.K[b], a.KT[b]); add(a.Vv[b], a.VT[b]);
+            if (dual) { add(a.Qd[b], a.QdT[b]); add(a.Kd[b], a.KdT[b]); add(a.Vd[b], a.VdT[b]); }
+            HC(transpose_bf16_jobs(J, BH, S, dh, (int)y.ld(dh), (int)y.ld(S), hrow, hcol, s));
+          }
+        } else {
+          HC(convs({{a.Qh, a.Q[b], a.QT[b]}, {a.Kh, a.K[b], a.KT[b]}, {a.Vh, a.Vv[b], a.VT[b]},
+                    {dual ? a.Qdh : nullptr, a.Qd[b], a.QdT[b]},
+                    {dual ? a.Kdh : nullptr, a.Kd[b], a.KdT[b]},
+                    {dual ? a.Vdh : nullptr, a.Vd[b], a.VdT[b]}},
+                   S, dh, BH, sh, hrow, hcol));
+        }
       }
       if (y.fused) {
         HC(attn_fwd(attn_args(b, Bn, dual, a), s));
