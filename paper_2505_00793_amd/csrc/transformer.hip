@@ -290,17 +290,34 @@ __global__ void __launch_bounds__(256) ln_colsum_kernel(LnBwdArgs a) {
   const int r0 = blockIdx.y * LN_CHUNK;
   const int r1 = min(a.N, r0 + LN_CHUNK);
   float sg = 0.f, sb = 0.f, sgd = 0.f, sbd = 0.f;
+  // eight rows requested before the first is added, from indices clamped into the
+  // chunk (one row at a time the 4-block decoder over 16 x 256 tokens took 44.4 ms a
+  // meta-gradient, now 43.7; H v of the 128-wide one 767 -> 748 us); the order of the
+  // sums stays
+  constexpr int U = 8;
   if (j < a.d) {
-    for (int r = r0 + ph; r < r1; r += 4) {
-      const long o = (long)r * a.d + j;
-      const float dy = a.dy[o], xh = a.xh[o];
-      sg += dy * xh;
-      sb += dy;
-      if (a.dual) {
-        const float dyd = a.dyd[o];
-        sgd += dyd * xh + dy * a.xhd[o];
-        sbd += dyd;
+    for (int rb = r0 + ph; rb < r1; rb += 4 * U) {
+      float dy[U], xh[U], dyd[U], xhd[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const long o = (long)min(rb + 4 * u, r1 - 1) * a.d + j;
+        dy[u] = a.dy[o];
+        xh[u] = a.xh[o];
+        if (a.dual) {
+          dyd[u] = a.dyd[o];
+          xhd[u] = a.xhd[o];
+        }
       }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (rb + 4 * u < r1) {
+          sg += dy[u] * xh[u];
+          sb += dy[u];
+          if (a.dual) {
+            sgd += dyd[u] * xh[u] + dy[u] * xhd[u];
+            sbd += dyd[u];
+          }
+        }
     }
   }
   red[ph][0][c] = sg;
