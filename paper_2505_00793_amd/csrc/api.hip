@@ -378,6 +378,7 @@ struct Eng {
       op.M = R;
       op.N = nout;
       op.K = p->kx(nin);
+      op.kpad = op.K - nin;
       op.ws = a.skws;
       op.ws_floats = a.skws_n;
       const int flags = G_C1 | (dual ? (G_BD | (l > 0 ? G_AD : 0)) : 0);
@@ -461,6 +462,7 @@ struct Eng {
       opw.M = nin;
       opw.N = nout;
       opw.K = p->kx(R);
+      opw.kpad = opw.K - R;
       const int flags_w = (need_c1 ? G_C1 : 0) | (dual ? (G_BD | (l > 0 ? G_AD : 0)) : 0);
       // backward-data product dA = dZ W^T (and its tangent), activation epilogue
       GemmOperands<T> opd;
@@ -475,6 +477,9 @@ struct Eng {
         opd.M = R;
         opd.N = nin;
         opd.K = p->kx(nout);
+        // (the output layer's padding is no sign of ragged widths: its products keep
+        // the walk of aligned ones)
+        opd.kpad = l == p->L - 1 ? 0 : opd.K - nout;
         e.Zp = a.Z[l - 1];
         e.Zdp = a.Zd[l - 1];
         e.Ap = a.A[l - 1];

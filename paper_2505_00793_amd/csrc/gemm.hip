@@ -176,6 +176,19 @@ __device__ __forceinline__ void zero_tile_pads(T* p, T* pd, int ld, T* pT, T* pd
     }
 }
 
+// Whether the epilogue of a 512-thread tile at the edge of the output preloads its
+// rows (load_rows_clamped) or takes them one by one (row), which loads 16 bytes at
+// a time from aligned rows and single elements, each behind a branch, from others.
+// Preloading is for float32 operands and for ragged products (padded contractions;
+// and any with unaligned rows).  Aligned bf16 products take their edges row by row:
+// no slower (4 x 1024 Adam network with a 100-wide head: 4.13 ms either way), and the
+// two walks do not round alike -- the compiler contracts Adam's b1 m + (1 - b1) g
+// onto the other product in row -- so a change of walk changes a network's bits.
+template <typename T>
+int preload_edge(const GemmOperands<T>& op) {
+  return sizeof(T) == 4 || op.kpad > 0;
+}
+
 template <typename T>
 struct ActFwdOp {
   EpiActFwd<T> e;
@@ -225,8 +238,10 @@ template <typename T>
 struct ActBwdOp {
   EpiActBwd<T> e;
   int M, N;
+  int edge;   // preload_edge of the product
   // the walk of an interior tile loads every row's z (zd) before the first row's stores
   static constexpr bool PRELOAD = true;
+  __device__ bool preload_edge() const { return edge || !aligned(); }
   struct In {
     float z[4], zd[4];
   };
@@ -339,8 +354,10 @@ template <typename T>
 struct ParamOp {
   ParamArgs<T> P;
   int M, N;
+  int edge;   // preload_edge of the product
   // the walk loads every row's inputs before the first row's arithmetic
   static constexpr bool PRELOAD = true;
+  __device__ bool preload_edge() const { return edge || !aligned(); }
   typedef ParamIn In;
   __device__ int n_trans() const { return P.outWT ? 1 : 0; }
   __device__ bool aligned() const { return (P.nout & 3) == 0 && (P.w_off & 3) == 0; }
@@ -481,6 +498,7 @@ struct ResidOp {
   // over k = 512 took 17.0 us, now 16.1 (8192 tokens, both products of a block:
   // 44.7 -> 39.1 us on average)
   static constexpr bool PRELOAD = true;
+  __device__ bool preload_edge() const { return true; }
   struct In {
     float h[4], hd[4];
   };
@@ -759,7 +777,7 @@ __device__ __forceinline__ void walk_tile(float* S1, float* S2, int mr0, int n0,
       walked = true;
     }
   }
-  if constexpr (Epi::PRELOAD && (NT == 256 || RP <= 64)) if (!walked) {
+  if constexpr (Epi::PRELOAD && (NT == 256 || RP <= 64)) if (!walked && (NT == 256 || epi.preload_edge())) {
     // Any tile: every row's inputs first (single elements from clamped indices,
     // no branch around a load), then the rows inside the output.
     constexpr int TPR = BN / 4;
@@ -1868,8 +1886,8 @@ hipError_t gemm_param_and_act_bwd(const GemmOperands<T>& opw, int flags_w, const
     if (gemm_pairs(opw, flags_w, opd, flags_d)) {
       const int kw = dma_tile_kind(opw), kd = dma_tile_kind(opd);
       {
-        const ParamOp<T> ew{P, P.nin, P.nout};
-        const ActBwdOp<T> ed{e, e.M, e.N};
+        const ParamOp<T> ew{P, P.nin, P.nout, preload_edge(opw)};
+        const ActBwdOp<T> ed{e, e.M, e.N, preload_edge(opd)};
         if (flags_w == G_C1 && flags_d == G_C1)
           return pair_by_tiles<G_C1, G_C1, T>(kw, kd, opw, ew, opd, ed, s);
         if (flags_w == (G_C1 | G_AD | G_BD) && flags_d == (G_C1 | G_AD | G_BD))
@@ -1910,12 +1928,12 @@ hipError_t gemm_act_fwd(const GemmOperands<T>& op, int flags, const EpiActFwd<T>
 template <typename T>
 hipError_t gemm_act_bwd(const GemmOperands<T>& op, int flags, const EpiActBwd<T>& epi,
                         hipStream_t s) {
-  return dispatch(op, flags, ActBwdOp<T>{epi, epi.M, epi.N}, s);
+  return dispatch(op, flags, ActBwdOp<T>{epi, epi.M, epi.N, preload_edge(op)}, s);
 }
 template <typename T>
 hipError_t gemm_param(const GemmOperands<T>& op, int flags, const ParamArgs<T>& P,
                       hipStream_t s) {
-  return dispatch(op, flags, ParamOp<T>{P, P.nin, P.nout}, s);
+  return dispatch(op, flags, ParamOp<T>{P, P.nin, P.nout, preload_edge(op)}, s);
 }
 
 #if !defined(GEMM_PART) || GEMM_PART == 8
@@ -1951,7 +1969,7 @@ hipError_t gemm_qkv_rope(const GemmOperands<bf16_t>& op, int flags, const EpiQkv
 hipError_t gemm_param_km(const GemmOperands<bf16_t>& op, int flags, const ParamArgs<bf16_t>& P,
                          hipStream_t s) {
   if (op.batch != 1 || P.b_off >= 0 || !km_ok(op)) return hipErrorInvalidValue;
-  const ParamOp<bf16_t> epi{P, P.nin, P.nout};
+  const ParamOp<bf16_t> epi{P, P.nin, P.nout, preload_edge(op)};
   if (flags == G_C1) return launch_param_km<G_C1>(op, epi, s);
   if (flags == (G_C1 | G_AD | G_BD)) return launch_param_km<G_C1 | G_AD | G_BD>(op, epi, s);
   return hipErrorInvalidValue;

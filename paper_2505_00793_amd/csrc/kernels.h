@@ -26,6 +26,7 @@ struct GemmOperands {
   const T* Bd;
   int lda, ldb;
   int M, N, K;
+  int kpad = 0;       // zero elements at the end of K (a contraction padded to 16 bytes)
   int batch = 1;      // independent products (grid.y); operand z starts at A + z * sA
   long sA = 0, sB = 0;
   // Optional float32 workspace for split-K (products with few output tiles and
