@@ -378,7 +378,6 @@ struct Eng {
       op.M = R;
       op.N = nout;
       op.K = p->kx(nin);
-      op.kpad = op.K - nin;
       op.ws = a.skws;
       op.ws_floats = a.skws_n;
       const int flags = G_C1 | (dual ? (G_BD | (l > 0 ? G_AD : 0)) : 0);
@@ -477,9 +476,6 @@ struct Eng {
         opd.M = R;
         opd.N = nin;
         opd.K = p->kx(nout);
-        // (the output layer's padding is no sign of ragged widths: its products keep
-        // the walk of aligned ones)
-        opd.kpad = l == p->L - 1 ? 0 : opd.K - nout;
         e.Zp = a.Z[l - 1];
         e.Zdp = a.Zd[l - 1];
         e.Ap = a.A[l - 1];

@@ -176,19 +176,6 @@ __device__ __forceinline__ void zero_tile_pads(T* p, T* pd, int ld, T* pT, T* pd
     }
 }
 
-// Whether the epilogue of a 512-thread tile at the edge of the output preloads its
-// rows (load_rows_clamped) or takes them one by one (row), which loads 16 bytes at
-// a time from aligned rows and single elements, each behind a branch, from others.
-// Preloading is for float32 operands and for ragged products (padded contractions;
-// and any with unaligned rows).  Aligned bf16 products take their edges row by row:
-// no slower (4 x 1024 Adam network with a 100-wide head: 4.13 ms either way), and the
-// two walks do not round alike -- the compiler contracts Adam's b1 m + (1 - b1) g
-// onto the other product in row -- so a change of walk changes a network's bits.
-template <typename T>
-int preload_edge(const GemmOperands<T>& op) {
-  return sizeof(T) == 4 || op.kpad > 0;
-}
-
 template <typename T>
 struct ActFwdOp {
   EpiActFwd<T> e;
@@ -238,10 +225,8 @@ template <typename T>
 struct ActBwdOp {
   EpiActBwd<T> e;
   int M, N;
-  int edge;   // preload_edge of the product
   // the walk of an interior tile loads every row's z (zd) before the first row's stores
   static constexpr bool PRELOAD = true;
-  __device__ bool preload_edge() const { return edge || !aligned(); }
   struct In {
     float z[4], zd[4];
   };
@@ -350,14 +335,24 @@ struct ActBwdOp {
   }
 };
 
+// Which of its two products Adam's update fuses into the sums of m and v where a
+// 512-thread tile is not wholly inside an output with 16-byte rows (param_finish).  A
+// bf16 network turns that last bit into 1e-4 of d eta over 16 steps, so it may not
+// depend on the walk a tile takes or on what the compiler picks there: the gradient's
+// product for contractions of whole 16-byte chunks, the state's for padded ones and
+// for float32 operands, as in the register-staged kernel, which took both before.
+template <typename T>
+int fuse_grad_at_edges(const GemmOperands<T>& op) {
+  return sizeof(T) == 2 && op.kpad == 0;
+}
+
 template <typename T>
 struct ParamOp {
   ParamArgs<T> P;
   int M, N;
-  int edge;   // preload_edge of the product
+  int edge_grad_fused;   // row_edge's rounding: see fuse_grad_at_edges
   // the walk loads every row's inputs before the first row's arithmetic
   static constexpr bool PRELOAD = true;
-  __device__ bool preload_edge() const { return edge || !aligned(); }
   typedef ParamIn In;
   __device__ int n_trans() const { return P.outWT ? 1 : 0; }
   __device__ bool aligned() const { return (P.nout & 3) == 0 && (P.w_off & 3) == 0; }
@@ -402,6 +397,13 @@ struct ParamOp {
                                          const float* c1, const float* c2, float* t1,
                                          float* t2) const {
     param_finish(P, P.w_off + (long)m * P.nout + n, cnt, in, c1, c2, t1);
+    if (P.outW) store_row4(P.outW, (long)m * P.ldW + n, cnt, t1);
+  }
+  // row_in at the edge of a 512-thread kernel's output
+  __device__ __forceinline__ void row_edge(int bz, int m, int n, int cnt, const ParamIn& in,
+                                           const float* c1, const float* c2, float* t1,
+                                           float* t2) const {
+    param_finish<true>(P, P.w_off + (long)m * P.nout + n, cnt, in, c1, c2, t1, edge_grad_fused);
     if (P.outW) store_row4(P.outW, (long)m * P.ldW + n, cnt, t1);
   }
   __device__ __forceinline__ void row(int bz, int m, int n, int cnt, const float* c1,
@@ -498,7 +500,6 @@ struct ResidOp {
   // over k = 512 took 17.0 us, now 16.1 (8192 tokens, both products of a block:
   // 44.7 -> 39.1 us on average)
   static constexpr bool PRELOAD = true;
-  __device__ bool preload_edge() const { return true; }
   struct In {
     float h[4], hd[4];
   };
@@ -777,7 +778,7 @@ __device__ __forceinline__ void walk_tile(float* S1, float* S2, int mr0, int n0,
       walked = true;
     }
   }
-  if constexpr (Epi::PRELOAD && (NT == 256 || RP <= 64)) if (!walked && (NT == 256 || epi.preload_edge())) {
+  if constexpr (Epi::PRELOAD && (NT == 256 || RP <= 64)) if (!walked) {
     // Any tile: every row's inputs first (single elements from clamped indices,
     // no branch around a load), then the rows inside the output.
     constexpr int TPR = BN / 4;
@@ -803,7 +804,10 @@ __device__ __forceinline__ void walk_tile(float* S1, float* S2, int mr0, int n0,
         } else {
           c2[0] = c2[1] = c2[2] = c2[3] = 0.0f;
         }
-        epi.row_in(bz, m, n, min(4, epi.N - n), in[it], c1, c2, t1, t2);
+        if constexpr (NT == 512 && IsParamOp<Epi>::value)
+          epi.row_edge(bz, m, n, min(4, epi.N - n), in[it], c1, c2, t1, t2);
+        else
+          epi.row_in(bz, m, n, min(4, epi.N - n), in[it], c1, c2, t1, t2);
         if (nT > 0) *reinterpret_cast<float4*>(S1 + si) = make_float4(t1[0], t1[1], t1[2], t1[3]);
         if (nT > 1) *reinterpret_cast<float4*>(S2 + si) = make_float4(t2[0], t2[1], t2[2], t2[3]);
       }
@@ -1886,8 +1890,8 @@ hipError_t gemm_param_and_act_bwd(const GemmOperands<T>& opw, int flags_w, const
     if (gemm_pairs(opw, flags_w, opd, flags_d)) {
       const int kw = dma_tile_kind(opw), kd = dma_tile_kind(opd);
       {
-        const ParamOp<T> ew{P, P.nin, P.nout, preload_edge(opw)};
-        const ActBwdOp<T> ed{e, e.M, e.N, preload_edge(opd)};
+        const ParamOp<T> ew{P, P.nin, P.nout, fuse_grad_at_edges(opw)};
+        const ActBwdOp<T> ed{e, e.M, e.N};
         if (flags_w == G_C1 && flags_d == G_C1)
           return pair_by_tiles<G_C1, G_C1, T>(kw, kd, opw, ew, opd, ed, s);
         if (flags_w == (G_C1 | G_AD | G_BD) && flags_d == (G_C1 | G_AD | G_BD))
@@ -1928,12 +1932,12 @@ hipError_t gemm_act_fwd(const GemmOperands<T>& op, int flags, const EpiActFwd<T>
 template <typename T>
 hipError_t gemm_act_bwd(const GemmOperands<T>& op, int flags, const EpiActBwd<T>& epi,
                         hipStream_t s) {
-  return dispatch(op, flags, ActBwdOp<T>{epi, epi.M, epi.N, preload_edge(op)}, s);
+  return dispatch(op, flags, ActBwdOp<T>{epi, epi.M, epi.N}, s);
 }
 template <typename T>
 hipError_t gemm_param(const GemmOperands<T>& op, int flags, const ParamArgs<T>& P,
                       hipStream_t s) {
-  return dispatch(op, flags, ParamOp<T>{P, P.nin, P.nout, preload_edge(op)}, s);
+  return dispatch(op, flags, ParamOp<T>{P, P.nin, P.nout, fuse_grad_at_edges(op)}, s);
 }
 
 #if !defined(GEMM_PART) || GEMM_PART == 8
@@ -1969,7 +1973,7 @@ hipError_t gemm_qkv_rope(const GemmOperands<bf16_t>& op, int flags, const EpiQkv
 hipError_t gemm_param_km(const GemmOperands<bf16_t>& op, int flags, const ParamArgs<bf16_t>& P,
                          hipStream_t s) {
   if (op.batch != 1 || P.b_off >= 0 || !km_ok(op)) return hipErrorInvalidValue;
-  const ParamOp<bf16_t> epi{P, P.nin, P.nout, preload_edge(op)};
+  const ParamOp<bf16_t> epi{P, P.nin, P.nout, fuse_grad_at_edges(op)};
   if (flags == G_C1) return launch_param_km<G_C1>(op, epi, s);
   if (flags == (G_C1 | G_AD | G_BD)) return launch_param_km<G_C1 | G_AD | G_BD>(op, epi, s);
   return hipErrorInvalidValue;

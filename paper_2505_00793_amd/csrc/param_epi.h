@@ -82,11 +82,12 @@ __device__ __forceinline__ void param_load(const ParamArgs<T>& P, long idx, int 
 // The arithmetic and stores for cnt (1..4) consecutive parameters at flat index
 // idx, given their inputs.  cv receives the values for the operand copies (new
 // theta for the update modes, the next tangent for the SGD seed/reverse modes,
-// 0 otherwise).
-template <typename T>
+// 0 otherwise).  EDGE: Adam's m and v with the gradient's product fused into the sum
+// (grad_fused) or the state's; else as the compiler contracts them.
+template <bool EDGE = false, typename T>
 __device__ __forceinline__ void param_finish(const ParamArgs<T>& P, long idx, int cnt,
                                              const ParamIn& in, const float* g, const float* hv,
-                                             float* cv) {
+                                             float* cv, int grad_fused = 0) {
   const bool vec = cnt == 4 && (idx & 3) == 0;
   switch (P.mode) {
     case P_UPD_SGD_PP:
@@ -107,8 +108,14 @@ __device__ __forceinline__ void param_finish(const ParamArgs<T>& P, long idx, in
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float m0 = P.m_in ? in.x[1][k] : 0.0f, v0 = P.v_in ? in.x[2][k] : 0.0f;
-        m[k] = P.b1 * m0 + (1.0f - P.b1) * g[k];
-        v[k] = P.b2 * v0 + (1.0f - P.b2) * g[k] * g[k];
+        if constexpr (EDGE) {
+          const float c1 = 1.0f - P.b1, c2g = (1.0f - P.b2) * g[k];
+          m[k] = grad_fused ? fmaf(c1, g[k], P.b1 * m0) : fmaf(P.b1, m0, c1 * g[k]);
+          v[k] = grad_fused ? fmaf(c2g, g[k], P.b2 * v0) : fmaf(P.b2, v0, c2g * g[k]);
+        } else {
+          m[k] = P.b1 * m0 + (1.0f - P.b1) * g[k];
+          v[k] = P.b2 * v0 + (1.0f - P.b2) * g[k] * g[k];
+        }
         const float u = (m[k] / P.k1) / (sqrtf(v[k] / P.k2) + P.eps);
         cv[k] = in.x[0][k] - lam * (u + om * in.x[0][k]);
       }
