@@ -7,8 +7,13 @@
 // of the sweep is one d x d matrix-vector product per phase, in one workgroup
 // (linreg_sweep_kernel).  Walking the batches themselves, 2 T + 1 of them, one
 // compute unit receives about 20 bytes a cycle: 130 features, 1000 rows, T = 3
-// took 620 us that way.  The validation loss is formed from its residuals (as a
-// quadratic form it would cancel near a fit).
+// took 620 us that way, 32 us this way.
+//
+// G, c and the whole sweep are float64.  Near a fit, or with features far from
+// zero mean, G theta - c cancels: from float32 matrices d eta lay up to six times as
+// far from the exact one as from float32 residuals (200 features, 50 rows, T = 2,
+// mean 3, at the fit: 7.1e-4 against 1.1e-4; now 5e-8).  The products of float32
+// values are exact in float64, so the sums are what rounds, at 1e-16.
 #include <algorithm>
 
 #include "kernels.h"
@@ -17,39 +22,42 @@ namespace mfmg {
 
 namespace {
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 constexpr int GR_MAXD = 256;
 constexpr int GR_MAXR = 1024;
 constexpr int GR_MAXT = 64;
 constexpr int GR_THREADS = 1024;
 constexpr int GR_WAVES = GR_THREADS / 64;
-constexpr int GR_SAVE = 8192;         // floats of inner gradients kept in LDS (T d)
 
 struct GramArgs {
   const float* xs[GR_MAXT + 1];   // the T training batches, then the validation batch
   const float* ys[GR_MAXT + 1];
   int T, rows, vrows, d;
-  int n, nr, ldg;                 // n = d + 1 columns [X | y]; rows (zero past n) and row
-                                  // pitch of G
-  float* G;                       // [T + 1][nr][ldg]
+  int nr, ldg;                    // rows (d + 1 in whole tiles) and row pitch of G
+  int rps, rounds;                // of the sweep: rows a step; rounds of R steps a phase
+  double* G;                      // [T + 1][nr][ldg], zero past row d
   const float* theta0;
   const float* eta;
-  float* gsave;                   // [T][d] inner gradients, when they do not fit LDS
-  float* thetaT;                  // [d], for linreg_val_kernel
-  float* vpart;                   // its partial sums
+  double* gsave;                  // [T][d] inner gradients
+  double* thetaT;                 // [d], for linreg_val_kernel
+  double* vpart;                  // its partial sums
   unsigned* ticket;
   float* d_eta;
   float* val_loss;
 };
 
-// [X | y]^T [X | y] of every batch: one workgroup per 32 x 32 output tile on or
+// [X | y]^T [X | y] of every batch: one workgroup per 16 x 16 output tile on or
 // above the diagonal, whose 16 waves take every 16th group of four rows; the
-// v_mfma_f32_16x16x4_f32 operands are read straight from the rows (lane: column
-// lane % 16 of row lane / 16, 64-byte runs), so no LDS staging is needed.  The
-// waves' sums are added in wave order in float64 and rounded once.
+// v_mfma_f64_16x16x4_f64 operands are read straight from the rows (lane: column
+// lane % 16 of row lane / 16, 64-byte runs), so no LDS staging is needed.  Small
+// tiles, because the batches are few: 130 features and T = 3 give 180 workgroups
+// (60 with 32 x 32 tiles, and four times the matrix work in each).  The waves' sums
+// are added in wave order.
 __global__ void __launch_bounds__(GR_THREADS) linreg_gram_kernel(GramArgs a) {
-  __shared__ float part[GR_WAVES][32 * 33];
+  __shared__ double part[GR_WAVES][16 * 17];
   const int b = blockIdx.y;
-  const int nt = a.nr / 32;
+  const int nt = a.nr / 16;
   int p = blockIdx.x, ti = 0;
   while (p >= nt - ti) {
     p -= nt - ti;
@@ -61,243 +69,193 @@ __global__ void __launch_bounds__(GR_THREADS) linreg_gram_kernel(GramArgs a) {
   const float* X = a.xs[b];
   const float* y = a.ys[b];
   const int rows = b < a.T ? a.rows : a.vrows;
-  // four columns per lane: two of the tile's rows, two of its columns
-  const float* base[4];
-  unsigned stride[4];
-  bool in[4];
+  // two columns per lane: one of the tile's rows, one of its columns
+  const float* base[2];
+  unsigned stride[2];
+  bool in[2];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int c = (q < 2 ? ti : tj) * 32 + (q & 1) * 16 + (lane & 15);
+  for (int q = 0; q < 2; ++q) {
+    const int c = (q == 0 ? ti : tj) * 16 + (lane & 15);
     base[q] = c < a.d ? X + c : y;
     stride[q] = c < a.d ? a.d : 1;
     in[q] = c <= a.d;
   }
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  constexpr int UN = 4;   // steps whose loads are in flight together
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  constexpr int UN = 8;   // steps whose loads are in flight together
   const int steps = (rows + 4 * GR_WAVES - 1) / (4 * GR_WAVES);
   for (int s0 = 0; s0 < steps; s0 += UN) {
-    float v[UN][4];
+    float v[UN][2];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       const int r = (s0 + u) * 4 * GR_WAVES + 4 * w + (lane >> 4);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[u][q] = base[q][(unsigned)min(r, rows - 1) * stride[q]];
+      for (int q = 0; q < 2; ++q) v[u][q] = base[q][(unsigned)min(r, rows - 1) * stride[q]];
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
+      if (s0 + u >= steps) break;
       const int r = (s0 + u) * 4 * GR_WAVES + 4 * w + (lane >> 4);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[u][q] = in[q] && r < rows ? v[u][q] : 0.0f;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u][i], v[u][2 + j], acc[i][j], 0, 0, 0);
+      for (int q = 0; q < 2; ++q) v[u][q] = in[q] && r < rows ? v[u][q] : 0.0f;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[u][0], (double)v[u][1], acc, 0, 0, 0);
     }
   }
+  // lane and element r of the result: row 4 r + lane / 16, column lane % 16
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        part[w][(i * 16 + (lane >> 4) * 4 + r) * 33 + j * 16 + (lane & 15)] = acc[i][j][r];
+  for (int r = 0; r < 4; ++r) part[w][(4 * r + (lane >> 4)) * 17 + (lane & 15)] = acc[r];
   __syncthreads();
-  float* G = a.G + (long)b * a.nr * a.ldg;
-  {
-    const int r = tid >> 5, c = tid & 31;
-    double s = 0.0;
+  if (tid >= 256) return;
+  double* G = a.G + (long)b * a.nr * a.ldg;
+  const int r = tid >> 4, c = tid & 15;
+  double s = 0.0;
 #pragma unroll
-    for (int k = 0; k < GR_WAVES; ++k) s += (double)part[k][r * 33 + c];
-    const float g = (float)s;
-    const int gr = ti * 32 + r, gc = tj * 32 + c;
-    if (gc < a.ldg) G[(long)gr * a.ldg + gc] = g;
-    if (ti != tj) part[0][r * 33 + c] = g;   // each thread rewrites the entry only it read
-  }
-  if (ti == tj) return;
-  __syncthreads();
-  const int r = tid >> 5, c = tid & 31;   // the mirrored tile
-  const int gr = tj * 32 + r, gc = ti * 32 + c;
-  if (gc < a.ldg) G[(long)gr * a.ldg + gc] = part[0][c * 33 + r];
+  for (int k = 0; k < GR_WAVES; ++k) s += part[k][r * 17 + c];
+  const int gr = ti * 16 + r, gc = tj * 16 + c;
+  if (gc < a.ldg) G[(long)gr * a.ldg + gc] = s;
+  if (ti != tj && gr < a.ldg) G[(long)gc * a.ldg + gr] = s;   // the mirrored tile
 }
 
-__device__ __forceinline__ float quad_sum(float v) {   // over the four lanes of a quad
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double quad_sum(double v) {   // over the four lanes of a quad
+  v += dpp_f64<0xB1>(v);
+  v += dpp_f64<0x4E>(v);
   return v;
 }
 
-// The sweep: T inner steps, the seed at theta_T, T reverse steps, on W waves.  A
-// row of G takes LPR lanes of 16 bytes, so the workgroup reads W * 64 / LPR rows
-// per step and all d in NS steps, each thread holding its NS pieces in registers;
-// the next phase's pieces are requested as soon as this phase's are used.  The
-// column sums go over the row slots of a wave, then over the W waves through LDS
-// (four lanes per column), in a fixed order.
-template <int W, int LPR, int NS, bool SAVE_LDS>
-__global__ void __launch_bounds__(W * 64) linreg_sweep_kernel(GramArgs a) {
-  constexpr int RPW = 64 / LPR;            // rows per wave and step
-  constexpr int RPS = W * RPW;
-  __shared__ float x[NS * RPS];            // the vector of this phase, zero past d
-  __shared__ __attribute__((aligned(16))) float part[W][LPR * 4];
-  __shared__ float gs[SAVE_LDS ? GR_SAVE : 1];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int d = a.d, T = a.T;
-  const int row0 = w * RPW + lane / LPR, cg = (lane % LPR) * 4;
-  float4 g[NS];
-  const unsigned off = (unsigned)(row0 * a.ldg + min(cg, a.ldg - 4)) * 4u;
-  auto load = [&](int b) {   // NS * RPS <= a.nr
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const float* G = a.G + ((long)b * a.nr + s * RPS) * a.ldg;
-      g[s] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(G) + off);
-    }
+// The sweep: T inner steps, the seed at theta_T, T reverse steps, in one workgroup of
+// NT threads.  The rows 0 .. d - 1 of G, each ldg / 2 pieces of 16 bytes, are read as
+// one run of pieces, rps whole rows a step (NT pieces but for a last part of a row): a
+// compute unit's loads bound the sweep (64 bytes a cycle), so none may be spent on
+// lanes past a row's end (a power of two of lanes per row, half of them past the end
+// at 130 features, took 3.1 us a phase there, this 1.8).  A thread keeps R pieces
+// in flight: a piece is replaced by the one R steps on, of the next phase's matrix at
+// the end.  The column sums go over a thread's steps, then over the rps rows of a step
+// through LDS (four lanes per column), in a fixed order.
+constexpr int GR_RPS = 32;      // most rows a step
+constexpr int GR_XROWS = 512;   // rows of all steps, at most
+
+template <int NT, int R>
+__global__ void __launch_bounds__(NT) linreg_sweep_kernel(GramArgs a) {
+  __shared__ double x[GR_XROWS];           // the vector of this phase, zero past d
+  __shared__ __attribute__((aligned(16))) double part[2 * NT];   // [rps][ldg]
+  const int tid = threadIdx.x;
+  const int d = a.d, T = a.T, ldg = a.ldg, cp = ldg >> 1;
+  const int rps = a.rps, span = rps * cp, rounds = a.rounds;
+  const int row0 = min(tid / cp, rps - 1);
+  const int last = a.nr * cp - 1;
+  double2 g[R];
+  // piece of step k0 + k; past G's rows its last one (x is zero there)
+  const int own_piece = min(tid, span - 1);
+  auto load = [&](int b, int k0, int k) {
+    const double2* G = reinterpret_cast<const double2*>(a.G) + (long)b * (last + 1);
+    g[k] = G[(unsigned)min((k0 + k) * span + own_piece, last)];
   };
-  // W * 16 columns at a time: thread 4 j + q works on column j
-  static_assert(W * 16 >= LPR * 4 || W * 32 >= LPR * 4, "one or two columns per thread");
-  constexpr int NC = W * 16 >= LPR * 4 ? 1 : 2;
-  const int q = tid & 3;
-  int j[NC];
-  bool own[NC];
+  // thread 4 j + q works on column j
+  const int q = tid & 3, j = min(tid >> 2, d - 1);
+  const bool own = (tid >> 2) < d && q == 0;
 #pragma unroll
-  for (int n = 0; n < NC; ++n) {
-    const int col = (tid >> 2) + n * W * 16;
-    j[n] = min(col, d - 1);
-    own[n] = col < d && q == 0;
-  }
-  load(0);
-  float c[NC], th[NC], tb[NC], eb[NC], lam[NC], u[NC];
-  auto rhs = [&](int b) {   // c_b
-#pragma unroll
-    for (int n = 0; n < NC; ++n) c[n] = a.G[((long)b * a.nr + d) * a.ldg + j[n]];
-  };
-  rhs(0);
-#pragma unroll
-  for (int n = 0; n < NC; ++n) {
-    th[n] = a.theta0[j[n]];
-    lam[n] = a.eta[j[n]];
-    eb[n] = 0.0f;
-  }
-  for (int i = tid; i < NS * RPS; i += W * 64) x[i] = 0.0f;
+  for (int k = 0; k < R; ++k) load(0, 0, k);
+  auto rhs = [&](int b) { return a.G[((long)b * a.nr + d) * ldg + j]; };   // c_b
+  double c = rhs(0), th = a.theta0[j], tb = 0.0, eb = 0.0;
+  const float eta = a.eta[j];
+  for (int i = tid; i < GR_XROWS; i += NT) x[i] = 0.0;
   __syncthreads();
-#pragma unroll
-  for (int n = 0; n < NC; ++n) {
-    lam[n] = expf(lam[n]);
-    if (own[n]) x[j[n]] = th[n];
-  }
+  const double lam = expf(eta);
+  if (own) x[j] = th;
   __syncthreads();
-  // u = G_b x; requests G of batch nb meanwhile
-  auto matvec = [&](int nb) {
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  const double inv = 2.0 / a.rows, invv = 2.0 / a.vrows;
+  // Phases 0 .. 2 T: the training batches, the validation batch, the training batches
+  // in reverse.
+#pragma unroll 1
+  for (int p = 0; p <= 2 * T; ++p) {
+    const int b = p <= T ? p : 2 * T - p;
+    const int nb = p < T ? p + 1 : max(2 * T - p - 1, 0);   // the next phase's
+    double gr = 0.0;
+    if (p > T && own) gr = a.gsave[(long)b * d + j];   // by the lane that saved it
+    double2 s = make_double2(0.0, 0.0);
+#pragma unroll 1
+    for (int n = 0; n < rounds; ++n) {
+      const bool more = n + 1 < rounds;
+      const int bn = more ? b : nb, kn = more ? (n + 1) * R : 0;
 #pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      const float xk = x[k * RPS + row0];
-      s.x = fmaf(g[k].x, xk, s.x);
-      s.y = fmaf(g[k].y, xk, s.y);
-      s.z = fmaf(g[k].z, xk, s.z);
-      s.w = fmaf(g[k].w, xk, s.w);
-    }
-    // from NS = 28 on, loads moved up between the products would not fit the registers
-    if (NS >= 28) __builtin_amdgcn_sched_barrier(0);
-    if (nb >= 0) load(nb);
-#pragma unroll
-    for (int o = LPR; o < 64; o <<= 1) {
-      s.x += __shfl_xor(s.x, o, 64);
-      s.y += __shfl_xor(s.y, o, 64);
-      s.z += __shfl_xor(s.z, o, 64);
-      s.w += __shfl_xor(s.w, o, 64);
-    }
-    if (lane < LPR) *reinterpret_cast<float4*>(&part[w][cg]) = s;
-    __syncthreads();
-#pragma unroll
-    for (int n = 0; n < NC; ++n) {
-      float t = 0.0f;
-#pragma unroll
-      for (int k = 0; k < W / 4; ++k) t += part[q * (W / 4) + k][j[n]];
-      u[n] = quad_sum(t);
-    }
-  };
-  const float inv = 2.0f / (float)a.rows, invv = 2.0f / (float)a.vrows;
-  for (int t = 0; t < T; ++t) {
-    matvec(t + 1);
-    float gr[NC];
-#pragma unroll
-    for (int n = 0; n < NC; ++n) gr[n] = inv * (u[n] - c[n]);
-    rhs(t + 1);
-#pragma unroll
-    for (int n = 0; n < NC; ++n) {
-      th[n] -= lam[n] * gr[n];
-      if (own[n]) {
-        x[j[n]] = th[n];
-        if (SAVE_LDS) gs[t * d + j[n]] = gr[n];
-        else a.gsave[(long)t * d + j[n]] = gr[n];
+      for (int k = 0; k < R; ++k) {
+        const double xk = x[(n * R + k) * rps + row0];
+        s.x = fma(g[k].x, xk, s.x);
+        s.y = fma(g[k].y, xk, s.y);
+        load(bn, kn, k);
       }
     }
+    if (tid < span) *reinterpret_cast<double2*>(&part[2 * tid]) = s;
+    __syncthreads();
+    double u = 0.0;   // column j of G_b x
+#pragma unroll
+    for (int k = 0; k < GR_RPS / 4; ++k) {
+      if (4 * k >= rps) break;
+      const double t = part[min(4 * k + q, rps - 1) * ldg + j];
+      u += 4 * k + q < rps ? t : 0.0;
+    }
+    u = quad_sum(u);
+    // x is rewritten now that every wave has passed the barrier after its last read
+    // of it; part, once every wave has passed the one below
+    if (p < T) {
+      gr = inv * (u - c);
+      c = rhs(p + 1);
+      th -= lam * gr;
+      if (own) {
+        x[j] = th;
+        a.gsave[(long)p * d + j] = gr;
+      }
+    } else {
+      if (p == T) {
+        if (a.val_loss && own) a.thetaT[j] = th;   // for linreg_val_kernel
+        tb = invv * (u - c);                       // the seed, dV/dtheta_T
+      } else {
+        eb = fma(-lam * gr, tb, eb);
+        tb += inv * u;
+      }
+      if (own) x[j] = -lam * tb;
+    }
     __syncthreads();
   }
-  if (a.val_loss) {   // for linreg_val_kernel
-#pragma unroll
-    for (int n = 0; n < NC; ++n)
-      if (own[n]) a.thetaT[j[n]] = th[n];
-  }
-  // Seed: bar theta_T = dV/dtheta_T.  x is rewritten once every wave has passed the
-  // barrier after its last read of it.
-  matvec(T - 1);
-#pragma unroll
-  for (int n = 0; n < NC; ++n) {
-    tb[n] = invv * (u[n] - c[n]);
-    if (own[n]) x[j[n]] = -lam[n] * tb[n];
-  }
-  __syncthreads();
-  for (int i = T - 1; i >= 0; --i) {
-    float gr[NC];
-#pragma unroll
-    for (int n = 0; n < NC; ++n) {   // by the lane that saved it
-      gr[n] = 0.0f;
-      if (own[n]) gr[n] = SAVE_LDS ? gs[i * d + j[n]] : a.gsave[(long)i * d + j[n]];
-    }
-    matvec(i - 1);
-#pragma unroll
-    for (int n = 0; n < NC; ++n) {
-      eb[n] = fmaf(-lam[n] * gr[n], tb[n], eb[n]);
-      tb[n] += inv * u[n];
-      if (own[n]) x[j[n]] = -lam[n] * tb[n];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int n = 0; n < NC; ++n)
-    if (own[n]) a.d_eta[j[n]] = eb[n];
+  if (own) a.d_eta[j] = (float)eb;
 }
 
-// The validation loss: one wave per row, the workgroups' sums added in order by the
-// last one to finish.  A launch of its own also for small batches: held in the
-// sweep's registers from its start the batch made the sweep longer by more (64 x
-// 256: 22 us against 14 and 8), its unrolled code running once.
+__device__ __forceinline__ double wave_sum_f64(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// The validation loss from its residuals: one wave per row, the workgroups' sums
+// added in order by the last one to finish.  A launch of its own also for small
+// batches: held in the sweep's registers from its start the batch made the sweep
+// longer by more, its unrolled code running once.
 __global__ void __launch_bounds__(256) linreg_val_kernel(GramArgs a) {
-  __shared__ float x[GR_MAXD];
-  __shared__ float red[4];
+  __shared__ double x[GR_MAXD];
+  __shared__ double red[4];
   __shared__ bool last;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const float* X = a.xs[a.T];
   const float* y = a.ys[a.T];
   if (tid < a.d) x[tid] = a.thetaT[tid];
   __syncthreads();
-  float ls = 0.0f;
+  double ls = 0.0;
   for (int r = blockIdx.x * 4 + w; r < a.vrows; r += gridDim.x * 4) {
     constexpr int NV = GR_MAXD / 64;
-    float xr[NV], s = 0.0f;
+    float xr[NV];
+    double s = 0.0;
     const float t = y[r];
 #pragma unroll
     for (int n = 0; n < NV; ++n) xr[n] = X[(long)r * a.d + min(lane + 64 * n, a.d - 1)];
 #pragma unroll
     for (int n = 0; n < NV; ++n)
-      if (lane + 64 * n < a.d) s = fmaf(xr[n], x[lane + 64 * n], s);
-    const float e = wave_sum(s) - t;
-    ls = fmaf(e, e, ls);
+      if (lane + 64 * n < a.d) s = fma((double)xr[n], x[lane + 64 * n], s);
+    const double e = wave_sum_f64(s) - t;
+    ls = fma(e, e, ls);
   }
   if (lane == 0) red[w] = ls;
   __syncthreads();
@@ -311,27 +269,29 @@ __global__ void __launch_bounds__(256) linreg_val_kernel(GramArgs a) {
   __syncthreads();
   if (!last || w != 0) return;
   __threadfence();
-  float s = 0.0f;
+  double s = 0.0;
   for (int k = lane; k < (int)gridDim.x; k += 64)
     s += __hip_atomic_load(a.vpart + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  s = wave_sum(s);
-  if (lane == 0) *a.val_loss = s / (float)a.vrows;
+  s = wave_sum_f64(s);
+  if (lane == 0) *a.val_loss = (float)(s / a.vrows);
 }
 
 constexpr int GR_VAL_BLOCKS = 256;
 
-template <int W, int LPR, int NS>
-void launch_sweep(const GramArgs& a, hipStream_t s) {
-  if ((long)a.T * a.d <= GR_SAVE)
-    hipLaunchKernelGGL((linreg_sweep_kernel<W, LPR, NS, true>), dim3(1), dim3(W * 64), 0, s, a);
-  else
-    hipLaunchKernelGGL((linreg_sweep_kernel<W, LPR, NS, false>), dim3(1), dim3(W * 64), 0, s, a);
+// R: the steps of a phase, or a half or third .. of them where these are more than 13
+// (4 registers each).
+template <int NT, int R = 1>
+hipError_t launch_sweep(const GramArgs& a, int r, hipStream_t s) {
+  if constexpr (R <= 13) {
+    if (r > R) return launch_sweep<NT, R + 1>(a, r, s);
+    hipLaunchKernelGGL((linreg_sweep_kernel<NT, R>), dim3(1), dim3(NT), 0, s, a);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
 
-inline long rup4(long n) { return (n + 3) / 4 * 4; }
-// Rows of G: d + 1 in whole 32-row tiles, and at least the 64 of the sweep's
-// smallest step, so that the sweep reads zeros and not past the end.
-inline int gram_rows(int d) { return std::max(64, (d + 1 + 31) / 32 * 32); }
+inline long rup2(long n) { return (n + 1) / 2 * 2; }
+inline int gram_rows(int d) { return (d + 1 + 15) / 16 * 16; }
 
 }  // namespace
 
@@ -340,8 +300,10 @@ static bool gram_fits(int T, int rows, int vrows, int d) {
          vrows >= 1 && vrows <= GR_MAXR;
 }
 
+// The arrays of GramArgs in order, all of even length (16-byte aligned).
 long linreg_scratch_floats(int T, int d) {   // covers the (T + 1) d of the other forms
-  return (T + 1) * (long)gram_rows(d) * rup4(d + 1) + rup4((long)T * d) + rup4(d) + GR_VAL_BLOCKS + 4;
+  return 2 * ((T + 1) * (long)gram_rows(d) * rup2(d + 1) + rup2((long)T * d) + rup2(d) +
+              GR_VAL_BLOCKS + 2);
 }
 
 hipError_t linreg_gram_meta_grad(const float* theta0, const float* eta, const float* const* xs,
@@ -357,26 +319,28 @@ hipError_t linreg_gram_meta_grad(const float* theta0, const float* eta, const fl
   a.xs[T] = vx;
   a.ys[T] = vy;
   a.T = T; a.rows = rows; a.vrows = vrows; a.d = d;
-  a.n = d + 1;
   a.nr = gram_rows(d);
-  a.ldg = (int)rup4(a.n);
-  a.G = scratch;
+  a.ldg = (int)rup2(d + 1);
+  a.G = reinterpret_cast<double*>(scratch);
   a.gsave = a.G + (long)(T + 1) * a.nr * a.ldg;
-  a.thetaT = a.gsave + rup4((long)T * d);
-  a.vpart = a.thetaT + rup4(d);
-  a.theta0 = theta0; a.eta = eta; a.d_eta = d_eta; a.val_loss = val_loss;
+  a.thetaT = a.gsave + rup2((long)T * d);
+  a.vpart = a.thetaT + rup2(d);
   a.ticket = reinterpret_cast<unsigned*>(a.vpart + GR_VAL_BLOCKS);
-  const int nt = a.nr / 32;
+  a.theta0 = theta0; a.eta = eta; a.d_eta = d_eta; a.val_loss = val_loss;
+  const int nt = a.nr / 16;
   hipLaunchKernelGGL(linreg_gram_kernel, dim3(nt * (nt + 1) / 2, T + 1), dim3(GR_THREADS), 0, s, a);
-  // waves, lanes per row of G, steps over its rows (steps x waves x 64 / lanes <=
-  // gram_rows)
-  if (d <= 64) launch_sweep<4, 16, 4>(a, s);
-  else if (d <= 96) launch_sweep<16, 32, 3>(a, s);
-  else if (d <= 128) launch_sweep<16, 32, 4>(a, s);
-  else if (d <= 160) launch_sweep<8, 64, 20>(a, s);
-  else if (d <= 192) launch_sweep<8, 64, 24>(a, s);
-  else if (d <= 224) launch_sweep<8, 64, 28>(a, s);
-  else launch_sweep<8, 64, 32>(a, s);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int threads = d <= 32 ? 128 : d <= 64 ? 512 : 1024;   // at least four per column
+  a.rps = std::min(threads / (a.ldg / 2), GR_RPS);
+  const int steps = (d + a.rps - 1) / a.rps;
+  a.rounds = (steps + 12) / 13;
+  const int r = (steps + a.rounds - 1) / a.rounds;
+  if (r * a.rounds * a.rps > GR_XROWS) return hipErrorInvalidValue;
+  e = threads == 128   ? launch_sweep<128>(a, r, s)
+      : threads == 512 ? launch_sweep<512>(a, r, s)
+                       : launch_sweep<1024>(a, r, s);
+  if (e != hipSuccess) return e;
   if (val_loss)
     hipLaunchKernelGGL(linreg_val_kernel, dim3(std::min((vrows + 3) / 4, GR_VAL_BLOCKS)),
                        dim3(256), 0, s, a);

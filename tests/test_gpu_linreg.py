@@ -1,5 +1,5 @@
 """Linear regression at the edges of its three forms (registers, staged batches, normal equations)
-against the float64 oracle."""
+and near a fit, against the float64 oracle."""
 import numpy as np
 import pytest
 
@@ -39,3 +39,39 @@ def test_linreg_forms(d, rows, val_rows, T):
     # in the worst order; 1e-5 leaves an order over what the forms show (5e-7 at T = 64)
     assert relerr(out.cpu().numpy(), ref) <= 1e-5
     assert abs(loss.item() - float(V)) <= 1e-5 * abs(float(V))
+
+
+@pytest.mark.parametrize("mean", [0.0, 3.0, 10.0])
+@pytest.mark.parametrize("d,rows,T", [(64, 700, 8), (97, 300, 2), (130, 1000, 3), (256, 1024, 4)])
+def test_normal_equations_at_a_fit(d, rows, T, mean):
+    """Where the gradient is small against G theta and X^T y, which it is the difference of."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2505_00793_amd import _lib as M
+    cfg = W.C1.with_(name="fit", cfg_id=142, widths=(d, 1), rows=rows, val_rows=rows - 50, T=T)
+    inp = W.make_inputs(cfg)
+    w = W.random_direction(d, 58).astype(np.float32)
+    w *= np.float32(np.sqrt(d)) / np.linalg.norm(w)
+    rng = np.random.default_rng(59)
+
+    def shifted(x):
+        x = (x + np.float32(mean)).astype(np.float32)
+        y = x.astype(np.float64) @ w + 0.1 * rng.standard_normal(len(x))
+        return x, y.astype(np.float32).reshape(-1, 1)
+
+    inp["train_x"], inp["train_y"] = map(list, zip(*[shifted(x) for x in inp["train_x"]]))
+    inp["val_x"], inp["val_y"] = shifted(inp["val_x"])
+    inp["theta0"] = w
+    inp["eta"] = np.full(d, np.log(0.01 / (1 + mean * mean * d / 4)), dtype=np.float32)
+    dev = to_device(inp)
+    P = M.Problem(desc_of(cfg))
+    out = torch.empty(d, device="cuda")
+    loss = torch.empty(1, device="cuda")
+    P.mfmg_meta_grad(dev["theta0"], None, dev["eta"], dev["xs"], dev["ys"], dev["vx"], dev["vy"],
+                     out, loss)
+    ref, V = oracle.meta_grad(cfg, inp)
+    # float64 but for exp(eta) and the result, two units of 6e-8 each, through T <= 8 steps that
+    # contract; float32 matrices show 4e-6 .. 8e-2 here, float32 residuals 4e-6 .. 7e-2
+    assert relerr(out.cpu().numpy(), ref) <= 1e-6
+    assert abs(loss.item() - float(V)) <= 1e-6 * abs(float(V))
