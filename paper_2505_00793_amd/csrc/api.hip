@@ -222,7 +222,8 @@ void plan_meta(const mfmg_problem* p, int T_, char* base, MetaPlan<T>& mp) {
   Carver c{base};
   mp.linreg_scratch = nullptr;
   if (p->linreg_path(T_)) {
-    mp.linreg_scratch = c.take<float>((size_t)linreg_scratch_floats(T_, p->w[0]));
+    mp.linreg_scratch = c.take<float>(
+        (size_t)linreg_scratch_floats(T_, p->d.rows, p->d.val_rows, p->w[0]));
     mp.static_bytes = c.off;
     mp.dynamic_bytes = 0;
     mp.total = c.off;

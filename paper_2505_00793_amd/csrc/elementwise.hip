@@ -674,8 +674,7 @@ __global__ void __launch_bounds__(1024) adam_reduce_kernel(const float* __restri
 // g = (2/N) X^T r, H v = (2/N) X^T rdot.
 // 512 threads.  The batches are used in the order of the sweep: the T
 // training batches, the validation batch, then the training batches again in
-// reverse.  Only batches small against d x d come here (linreg_meta_grad), so
-// each fits in LDS (80 KB); it is staged there with rows padded to a
+// reverse.  Each fits in LDS (80 KB; linreg_form); it is staged there with rows padded to a
 // pitch of 16 (mod 32) floats, so that the four rows a quarter-wave reads with
 // 16-byte accesses fall on distinct banks; the next batch's values are loaded
 // into registers while the current one is used, so the sweep waits on global
@@ -684,24 +683,23 @@ __global__ void __launch_bounds__(1024) adam_reduce_kernel(const float* __restri
 // group of the row, then a sum over the four lanes), X^T r takes 16-byte column
 // groups x 32 row groups per pass with an ordered sum of the 32 partials.
 // ------------------------------------------------------------------------------------
-constexpr int LR_MAXD = 256;
-constexpr int LR_MAXR = 1024;
-constexpr int LR_MAXT = 64;
+constexpr int LR_MAXD = LINREG_MAXD;
+constexpr int LR_MAXR = LINREG_MAXR;
 constexpr int LR_THREADS = 512;
-constexpr int LR_DIRECT_D = 224, LR_DIRECT_ROWS = 64;   // rows of a batch linreg_kernel takes
-static_assert(LR_DIRECT_ROWS <= LR_THREADS, "one target per thread");
+constexpr int LR_YPT = LR_MAXR / LR_THREADS;   // targets per thread
 constexpr int LR_STAGE = 20480;  // floats of one batch staged in LDS, rows padded (80 KB)
 constexpr int LR_PF = LR_STAGE / LR_THREADS;  // prefetched floats per thread (n <= LR_STAGE)
 constexpr int LR_PF4 = LR_PF / 4;             // prefetched 16-byte groups per thread
 constexpr int LR_CKPT = 4096;    // floats of checkpoints kept in LDS
+// 16 bytes at a 4-byte aligned address (batches need no more; one load all the same)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 struct LinregArgs {
   const float* theta0;
   const float* eta;
-  const float* xs[LR_MAXT];  // device pointers of the T training batches
-  const float* ys[LR_MAXT];
+  const float* xs[LINREG_MAXT];  // device pointers of the T training batches
+  const float* ys[LINREG_MAXT];
   int T, rows, d, vrows;
-  int vec;                   // every batch 16-byte aligned and d % 4 == 0
   const float* vx;
   const float* vy;
   float* d_eta;
@@ -714,7 +712,6 @@ __host__ __device__ __forceinline__ int lr_spitch(int d) {
   const int p = (d + 3) & ~3;
   return p + ((16 - (p & 31)) & 31);
 }
-static_assert(LR_DIRECT_ROWS * (LR_MAXD + 16) <= LR_STAGE, "every batch is staged");
 
 // Batch k of the sweep (k = 0 .. 2T).
 struct LrBatch {
@@ -729,30 +726,31 @@ __device__ __forceinline__ LrBatch lr_batch(const LinregArgs& a, int k) {
 }
 
 // Registers holding one batch on its way to LDS: 16-byte group tid + u *
-// LR_THREADS of X (vec), or element tid + u * LR_THREADS, and y[tid].  The
+// LR_THREADS of X (VEC), or element tid + u * LR_THREADS, and y[tid], ...  The
 // loads are unconditional (an index past the end reads the last element) so
 // that a register is never both cleared and loaded: the compiler would then
 // wait for every load in flight.
 struct LrRegs {
-  float x[LR_PF];   // vec: group u in x[4u .. 4u + 3]
-  float y;
+  float x[LR_PF];   // VEC: group u in x[4u .. 4u + 3]
+  float y[LR_YPT];
 };
 template <bool VEC>
 __device__ __forceinline__ void lr_load(const LrBatch& b, int d, LrRegs& g) {
   const int tid = threadIdx.x;
   const int n = b.rows * d;
   if constexpr (VEC) {
-    const float4* X4 = reinterpret_cast<const float4*>(b.X);
+    const f32x4u* X4 = reinterpret_cast<const f32x4u*>(b.X);
 #pragma unroll
     for (int u = 0; u < LR_PF4; ++u) {
-      const float4 v = X4[min(tid + u * LR_THREADS, n / 4 - 1)];
+      const f32x4u v = X4[min(tid + u * LR_THREADS, n / 4 - 1)];
       g.x[4 * u] = v.x; g.x[4 * u + 1] = v.y; g.x[4 * u + 2] = v.z; g.x[4 * u + 3] = v.w;
     }
   } else {
 #pragma unroll
     for (int u = 0; u < LR_PF; ++u) g.x[u] = b.X[min(tid + u * LR_THREADS, n - 1)];
   }
-  g.y = b.y[min(tid, b.rows - 1)];
+#pragma unroll
+  for (int v = 0; v < LR_YPT; ++v) g.y[v] = b.y[min(tid + v * LR_THREADS, b.rows - 1)];
 }
 // Registers -> LDS (padded rows; the padding columns stay zero).  Callers
 // synchronise before (the previous batch's readers are done) and after.
@@ -760,7 +758,9 @@ template <bool VEC>
 __device__ __forceinline__ void lr_commit(const LrBatch& b, int d, const LrRegs& g, float* stage,
                                           float* ys) {
   const int tid = threadIdx.x;
-  if (tid < b.rows) ys[tid] = g.y;
+#pragma unroll
+  for (int v = 0; v < LR_YPT; ++v)
+    if (tid + v * LR_THREADS < b.rows) ys[tid + v * LR_THREADS] = g.y[v];
   const int n = b.rows * d, P = lr_spitch(d);
   // element i = row * d + col goes to row * P + col; row and col advance by the
   // elements of one step without a division
@@ -916,7 +916,7 @@ __device__ float lr_pass(const LrBatch& b, int d, const float* stage, const floa
   return sq;
 }
 
-// VEC: every batch 16-byte aligned and d % 4 == 0 (16-byte prefetch loads).  The
+// VEC: d % 4 == 0 (16-byte prefetch loads).  The
 // two forms are separate kernels so that the prefetch has one load site, whose
 // registers the compiler then carries across the phase without copying them
 // (a copy would wait for the loads it was meant to overlap).
@@ -927,7 +927,7 @@ __global__ void __launch_bounds__(LR_THREADS) linreg_kernel(LinregArgs a) {
   __shared__ __attribute__((aligned(16))) float th[LR_MAXD], vv[LR_MAXD];
   __shared__ float tb[LR_MAXD], lam[LR_MAXD], eb[LR_MAXD];
   __shared__ float gs[LR_MAXD], hs[LR_MAXD];
-  __shared__ float r[LR_DIRECT_ROWS], rd[LR_DIRECT_ROWS], ys[LR_DIRECT_ROWS];
+  __shared__ float r[LR_MAXR], rd[LR_MAXR], ys[LR_MAXR];
   constexpr int NPART = LR_CRG * 4 * LR_CG;
   __shared__ __attribute__((aligned(16))) float part[NPART], part2[NPART];
   __shared__ float red[LR_THREADS / 64];
@@ -1002,7 +1002,7 @@ __global__ void __launch_bounds__(LR_THREADS) linreg_kernel(LinregArgs a) {
 }
 
 // The same meta-gradient with each batch held in registers, for d <= 64 with
-// d % 4 == 0, at most 256 rows in every batch and 16-byte aligned batches.
+// d % 4 == 0 and at most 256 rows in every batch.
 // Thread (q, c) = (tid / 16, tid % 16) holds the 16-byte group c of rows q,
 // q + 32, .., q + 224 (32 registers); the 16 groups of a row lie in one DPP row
 // of 16 lanes, which sums the row's dot products with rotations, so a residual
@@ -1025,7 +1025,7 @@ struct LrrRegs {
   float y;            // y of row q + 32 (c % 8)
 };
 struct LrrSrc {
-  const float4* x;
+  const f32x4u* x;
   const float* y;
   int n4, rows;
 };
@@ -1035,11 +1035,12 @@ struct LrrLoad {
 };
 
 __device__ __forceinline__ LrrSrc lrr_src(const LrBatch& b, int g4) {
-  return {reinterpret_cast<const float4*>(b.X), b.y, b.rows * g4, b.rows};
+  return {reinterpret_cast<const f32x4u*>(b.X), b.y, b.rows * g4, b.rows};
 }
 // Loads past the end read the last element (never cleared registers, see LrRegs).
 __device__ __forceinline__ float4 lrr_group(const LrrSrc& s, int g4, int q, int c, int u) {
-  return s.x[min((q + LRR_SLOTS * u) * g4 + c, s.n4 - 1)];
+  const f32x4u v = s.x[min((q + LRR_SLOTS * u) * g4 + c, s.n4 - 1)];
+  return make_float4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ float lrr_target(const LrrSrc& s, int q, int c) {
   return s.y[min(q + LRR_SLOTS * (c & 7), s.rows - 1)];
@@ -1418,18 +1419,48 @@ hipError_t adam_reduce(const float* partial, const int* block_offsets, int n_lay
 }
 
 bool linreg_fits(int T, int rows, int vrows, int d) {
-  return T >= 1 && T <= LR_MAXT && d >= 1 && d <= LR_MAXD && rows >= 1 && rows <= LR_MAXR &&
+  return T >= 1 && T <= LINREG_MAXT && d >= 1 && d <= LR_MAXD && rows >= 1 && rows <= LR_MAXR &&
          vrows >= 1 && vrows <= LR_MAXR;
+}
+
+// Which form is the fastest, from the calls' times in us.  Registers against the
+// normal equations: 64 features x 256 rows T = 4 16 against 18, T = 8 29 against 23.
+// Staging starts faster (one launch) but costs more a phase (2 T + 1 phases), with
+// 16-byte loads up to about 200 features: 128 x 142 T = 1 14 against 18, T = 2 22
+// against 21; 176 x 32 T = 2 25 against 27; 192 x 32 T = 3 35 against 37, T = 4 44 each; 192 x 98 T = 2 29 against
+// 30, T = 3 39 against 37; 224 x 32 T = 4 50 against 52; 224 x 85 T = 3 43 each, T = 4
+// 54 against 53; 256 x 64 T = 8 92 against 120.  Its single-element
+// loads of other widths take 3 us more: 130 x 142 T = 1 21 against 18, 190 x 98 T = 1
+// 22 against 23.  Batches that LDS does not hold go through the normal equations at
+// any T (256 x 256, T = 1: 33 against 116 in one workgroup).
+LinregForm linreg_form(int T, int rows, int vrows, int d) {
+  const int r = std::max(rows, vrows);
+  const bool vec = d % 4 == 0;
+  if (vec && d <= LRR_MAXD && r <= LRR_MAXROWS && T <= LRR_MAXT) return LinregForm::Registers;
+  const int most = d > 224 ? LINREG_MAXT   // T up to which staging is faster
+                   : vec   ? (d < 184 ? 1 : d < 208 ? 2 : 3) + (d >= 168 && r <= 48 ? 1 : 0)
+                           : (d <= 64 || d >= 184 ? 1 : 0);
+  return T <= most && r * lr_spitch(d) <= LR_STAGE ? LinregForm::Staged : LinregForm::Gram;
+}
+
+long linreg_scratch_floats(int T, int rows, int vrows, int d) {
+  return linreg_form(T, rows, vrows, d) == LinregForm::Gram ? linreg_gram_scratch_floats(T, d)
+                                                            : (T + 1) * (long)d;
 }
 
 hipError_t linreg_meta_grad(const float* theta0, const float* eta, const float* const* xs,
                             const float* const* ys, int T, int rows, int d, const float* vx,
                             const float* vy, int vrows, float* d_eta, float* val_loss,
                             float* scratch, hipStream_t s) {
+  if (!linreg_fits(T, rows, vrows, d)) return hipErrorInvalidValue;
+  const LinregForm form = linreg_form(T, rows, vrows, d);
+  if (form == LinregForm::Gram)
+    return linreg_gram_meta_grad(theta0, eta, xs, ys, T, rows, d, vx, vy, vrows, d_eta, val_loss,
+                                 scratch, s);
   LinregArgs a;
   a.theta0 = theta0;
   a.eta = eta;
-  for (int t = 0; t < LR_MAXT; ++t) {
+  for (int t = 0; t < LINREG_MAXT; ++t) {
     a.xs[t] = t < T ? xs[t] : nullptr;
     a.ys[t] = t < T ? ys[t] : nullptr;
   }
@@ -1437,33 +1468,18 @@ hipError_t linreg_meta_grad(const float* theta0, const float* eta, const float* 
   a.rows = rows;
   a.d = d;
   a.vrows = vrows;
-  bool vec = (d % 4) == 0 && (reinterpret_cast<uintptr_t>(vx) & 15) == 0;
-  for (int t = 0; t < T; ++t) vec = vec && (reinterpret_cast<uintptr_t>(xs[t]) & 15) == 0;
-  a.vec = vec ? 1 : 0;
   a.vx = vx;
   a.vy = vy;
   a.d_eta = d_eta;
   a.val_loss = val_loss;
   a.ckpt = scratch;
-  // One workgroup pays about 1.6 us a phase (2 T + 1 phases) to walk a batch in its
-  // registers, the normal equations 0.5 us after some 18 us for the matrices and
-  // three launches: 64 features, 256 rows: T = 4 17 against 25 us, T = 8 29 against
-  // 23 (64 rows), T = 64 206 against 71.
-  if (a.vec && d <= LRR_MAXD && rows <= LRR_MAXROWS && vrows <= LRR_MAXROWS && T <= LRR_MAXT) {
+  if (form == LinregForm::Registers)
     hipLaunchKernelGGL(linreg_reg_kernel, dim3(1), dim3(LR_THREADS), 0, s, a);
-    return hipGetLastError();
-  }
-  // Batches much smaller than their d x d matrices: 256 features, 64 rows, T = 4: 52
-  // against 69 us (200 features, 50 rows: 51 against 41; 256 rows: 324 against 70).
-  if (d > LR_DIRECT_D && rows <= LR_DIRECT_ROWS && vrows <= LR_DIRECT_ROWS) {
-    if (a.vec)
-      hipLaunchKernelGGL(linreg_kernel<true>, dim3(1), dim3(LR_THREADS), 0, s, a);
-    else
-      hipLaunchKernelGGL(linreg_kernel<false>, dim3(1), dim3(LR_THREADS), 0, s, a);
-    return hipGetLastError();
-  }
-  return linreg_gram_meta_grad(theta0, eta, xs, ys, T, rows, d, vx, vy, vrows, d_eta, val_loss,
-                               scratch, s);
+  else if (d % 4 == 0)
+    hipLaunchKernelGGL(linreg_kernel<true>, dim3(1), dim3(LR_THREADS), 0, s, a);
+  else
+    hipLaunchKernelGGL(linreg_kernel<false>, dim3(1), dim3(LR_THREADS), 0, s, a);
+  return hipGetLastError();
 }
 
 template hipError_t convert_matrices<bf16_t>(const ConvJobs<bf16_t>&, int, int, int, int, int, hipStream_t, int, long, long, long);

@@ -325,14 +325,20 @@ hipError_t adam_reduce(const float* partial, const int* block_offsets, int n_lay
 
 // Linear regression, SGD with per-parameter log learning rates, squared loss:
 // the whole meta-gradient.  xs, ys: host arrays of T device pointers; scratch:
-// linreg_scratch_floats(T, d) floats of device memory.
+// linreg_scratch_floats(T, rows, vrows, d) floats of device memory.
+constexpr int LINREG_MAXD = 256, LINREG_MAXR = 1024, LINREG_MAXT = 64;
 hipError_t linreg_meta_grad(const float* theta0, const float* eta, const float* const* xs,
                             const float* const* ys, int T, int rows, int d, const float* vx,
                             const float* vy, int vrows, float* d_eta, float* val_loss,
                             float* scratch, hipStream_t s);
 bool linreg_fits(int T, int rows, int vrows, int d);
-long linreg_scratch_floats(int T, int d);
-// Its form through the normal equations of the batches (linreg.hip).
+// Its three forms, chosen by the sizes alone (so that the scratch is the chosen
+// form's): every batch in registers, or staged in LDS, of one workgroup; or through
+// the normal equations of the batches (linreg.hip).
+enum class LinregForm { Registers, Staged, Gram };
+LinregForm linreg_form(int T, int rows, int vrows, int d);
+long linreg_scratch_floats(int T, int rows, int vrows, int d);
+long linreg_gram_scratch_floats(int T, int d);
 hipError_t linreg_gram_meta_grad(const float* theta0, const float* eta, const float* const* xs,
                                  const float* const* ys, int T, int rows, int d, const float* vx,
                                  const float* vy, int vrows, float* d_eta, float* val_loss,

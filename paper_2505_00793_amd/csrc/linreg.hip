@@ -24,15 +24,12 @@ namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-constexpr int GR_MAXD = 256;
-constexpr int GR_MAXR = 1024;
-constexpr int GR_MAXT = 64;
 constexpr int GR_THREADS = 1024;
 constexpr int GR_WAVES = GR_THREADS / 64;
 
 struct GramArgs {
-  const float* xs[GR_MAXT + 1];   // the T training batches, then the validation batch
-  const float* ys[GR_MAXT + 1];
+  const float* xs[LINREG_MAXT + 1];   // the T training batches, then the validation batch
+  const float* ys[LINREG_MAXT + 1];
   int T, rows, vrows, d;
   int nr, ldg;                    // rows (d + 1 in whole tiles) and row pitch of G
   int rps, rounds;                // of the sweep: rows a step; rounds of R steps a phase
@@ -235,7 +232,7 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 // batches: held in the sweep's registers from its start the batch made the sweep
 // longer by more, its unrolled code running once.
 __global__ void __launch_bounds__(256) linreg_val_kernel(GramArgs a) {
-  __shared__ double x[GR_MAXD];
+  __shared__ double x[LINREG_MAXD];
   __shared__ double red[4];
   __shared__ bool last;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -245,7 +242,7 @@ __global__ void __launch_bounds__(256) linreg_val_kernel(GramArgs a) {
   __syncthreads();
   double ls = 0.0;
   for (int r = blockIdx.x * 4 + w; r < a.vrows; r += gridDim.x * 4) {
-    constexpr int NV = GR_MAXD / 64;
+    constexpr int NV = LINREG_MAXD / 64;
     float xr[NV];
     double s = 0.0;
     const float t = y[r];
@@ -295,13 +292,8 @@ inline int gram_rows(int d) { return (d + 1 + 15) / 16 * 16; }
 
 }  // namespace
 
-static bool gram_fits(int T, int rows, int vrows, int d) {
-  return T >= 1 && T <= GR_MAXT && d >= 1 && d <= GR_MAXD && rows >= 1 && rows <= GR_MAXR &&
-         vrows >= 1 && vrows <= GR_MAXR;
-}
-
 // The arrays of GramArgs in order, all of even length (16-byte aligned).
-long linreg_scratch_floats(int T, int d) {   // covers the (T + 1) d of the other forms
+long linreg_gram_scratch_floats(int T, int d) {
   return 2 * ((T + 1) * (long)gram_rows(d) * rup2(d + 1) + rup2((long)T * d) + rup2(d) +
               GR_VAL_BLOCKS + 2);
 }
@@ -310,7 +302,7 @@ hipError_t linreg_gram_meta_grad(const float* theta0, const float* eta, const fl
                                  const float* const* ys, int T, int rows, int d, const float* vx,
                                  const float* vy, int vrows, float* d_eta, float* val_loss,
                                  float* scratch, hipStream_t s) {
-  if (!gram_fits(T, rows, vrows, d)) return hipErrorInvalidValue;
+  if (!linreg_fits(T, rows, vrows, d)) return hipErrorInvalidValue;
   GramArgs a = {};
   for (int t = 0; t < T; ++t) {
     a.xs[t] = xs[t];

@@ -15,11 +15,25 @@ CASES = [
     (63, 64, 64, 3), (65, 33, 40, 3), (96, 100, 7, 2), (97, 70, 257, 2), (128, 1024, 128, 2),
     (129, 90, 90, 64), (160, 61, 20, 2), (161, 130, 64, 2), (193, 65, 65, 2), (224, 64, 64, 2),
     (225, 64, 64, 2), (227, 65, 3, 2), (256, 64, 64, 16), (256, 300, 64, 34), (251, 7, 64, 3),
+    # staged for few steps: both sides of the widths, rows and steps where the rule changes
+    (16, 1024, 700, 1), (64, 257, 30, 1), (63, 256, 200, 1), (100, 182, 182, 1), (100, 183, 64, 1),
+    (180, 116, 40, 1), (180, 40, 40, 2), (184, 98, 98, 2), (204, 98, 10, 3), (208, 85, 85, 3),
+    (224, 85, 86, 3), (224, 48, 30, 4), (224, 49, 30, 4), (190, 98, 5, 1), (189, 90, 90, 2),
 ]
 
 
-@pytest.mark.parametrize("d,rows,val_rows,T", CASES)
-def test_linreg_forms(d, rows, val_rows, T):
+def off16(t):
+    """A copy of t that starts 4 bytes past a 16-byte boundary."""
+    import torch
+    buf = torch.empty(t.numel() + 1, device=t.device)
+    buf[1:] = t.reshape(-1)
+    return buf[1:].reshape(t.shape)
+
+
+@pytest.mark.parametrize("d,rows,val_rows,T,aligned", [(*c, True) for c in CASES] + [
+    (64, 256, 256, 6, False), (36, 100, 50, 2, False), (100, 182, 182, 1, False),
+    (256, 64, 64, 2, False), (130, 90, 90, 2, False)])
+def test_linreg_forms(d, rows, val_rows, T, aligned):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -27,6 +41,8 @@ def test_linreg_forms(d, rows, val_rows, T):
     cfg = W.C1.with_(name="lr", cfg_id=141, widths=(d, 1), rows=rows, val_rows=val_rows, T=T)
     inp = W.make_inputs(cfg)
     dev = to_device(inp)
+    if not aligned:
+        dev["xs"], dev["vx"] = [off16(x) for x in dev["xs"]], off16(dev["vx"])
     P = M.Problem(desc_of(cfg))
     ws = P.workspace(P.mfmg_query_sizes(T).workspace_bytes)
     ws.fill_(255)   # NaN
