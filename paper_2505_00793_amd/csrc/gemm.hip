@@ -1567,8 +1567,8 @@ bool dma_ok(const GemmOperands<T>& op) {
 // K-major operands the direct-to-LDS loads can address (any K).
 bool km_ok(const GemmOperands<bf16_t>& o) {
   auto ok = [&](const bf16_t* p, int cols, int ld, long stride) {
-    return !p || (!(reinterpret_cast<uintptr_t>(p) & 15) && ld % 8 == 0 && ld < (1 << 20) &&
-                  ld >= cols && stride % 8 == 0 && ((long)o.K * ld) * 2 < (1L << 31));
+    return !p || (!(reinterpret_cast<uintptr_t>(p) & 15) && ld % 8 == 0 && ld >= cols &&
+                  stride % 8 == 0 && gemm_km_fits(o.K, ld));
   };
   return o.K > 0 && ok(o.A, o.M, o.lda, o.sA) && ok(o.Ad, o.M, o.lda, o.sA) &&
          ok(o.B, o.N, o.ldb, o.sB) && ok(o.Bd, o.N, o.ldb, o.sB);

@@ -222,8 +222,14 @@ hipError_t gemm_qkv_rope(const GemmOperands<bf16_t>& op, int flags, const EpiQkv
                          hipStream_t s);
 // Weight gradients of operands stored with the contraction index outermost: C1 = A^T B
 // of A [K][lda], B [K][ldb] (and their tangents), for matrices without a bias
-// (P.b_off < 0); 16-byte aligned, leading dimensions multiples of 8, each operand
-// under 2 GB, any K.
+// (P.b_off < 0); 16-byte aligned, leading dimensions multiples of 8, operands that
+// gemm_km_fits, any K.
+// Operands of K rows of ld elements: under 2 GB, and rows short enough that the byte
+// offset of the last k step's 63 rows past K stays in 32 bits.  The planner leaves
+// transposed copies out by this rule and gemm_param_km refuses by it.
+inline bool gemm_km_fits(long K, long ld) {
+  return ld < (1L << 20) && K * ld * (long)sizeof(bf16_t) < (1L << 31);
+}
 hipError_t gemm_param_km(const GemmOperands<bf16_t>& op, int flags, const ParamArgs<bf16_t>& P,
                          hipStream_t s);
 // A layer's backward-weight product (with the parameter epilogue) and its

@@ -49,7 +49,7 @@ constexpr int MAXB = 16;
 struct Lay {
   int d, H, dh, F, V, S, Bt, Bv, L, mh, VE, fused, remat;
   // the weight gradients read their operands as stored by token (gemm_param_km),
-  // so no transposed copies of them exist: bf16, every operand under 2 GB
+  // so no transposed copies of them exist: bf16, every operand within gemm_km_fits
   bool km;
   float eps, lr;
   double base;
@@ -78,7 +78,7 @@ Lay make_lay(const mfmg_problem_desc& D) {
   y.VE = D.precision == MFMG_PREC_BF16 ? 8 : 4;
   y.fused = D.fused_attention;
   y.remat = D.block_remat;
-  y.km = y.VE == 8 && (long)y.maxB() * y.S * y.ld(std::max({3 * y.d, y.F, y.V})) * 2 < (1L << 31);
+  y.km = y.VE == 8 && gemm_km_fits((long)y.maxB() * y.S, y.ld(std::max({3 * y.d, y.F, y.V})));
   y.eps = D.ln_eps;
   y.lr = D.sgd_lr;
   y.base = D.rope_base;
