@@ -170,7 +170,9 @@ void carve_act(const mfmg_problem* p, Carver& c, Act<T>& a, int R, bool dual) {
     a.dZdT[k] = dual ? c.take<T>((size_t)maxw * p->ld(R)) : nullptr;
   }
   a.loss_rows = c.take<float>(R);
-  // float32 forward products with few output tiles and a long k run split-K
+  // float32 forward products with few output tiles and a long k run split-K, if k
+  // needs no padding (a ragged k has no slices of whole 16-byte chunks, and forward
+  // gives such a layer no scratch, whatever the other layers plan)
   long ws = 0;
   if (!p->bf16()) {
     for (int l = 0; l < L; ++l) {
@@ -379,8 +381,10 @@ struct Eng {
       op.M = R;
       op.N = nout;
       op.K = p->kx(nin);
-      op.ws = a.skws;
-      op.ws_floats = a.skws_n;
+      if (op.K == nin) {   // as planned (carve_act)
+        op.ws = a.skws;
+        op.ws_floats = a.skws_n;
+      }
       const int flags = G_C1 | (dual ? (G_BD | (l > 0 ? G_AD : 0)) : 0);
       EpiActFwd<T> e;
       e.bias = th.b[l];
