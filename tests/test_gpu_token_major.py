@@ -15,6 +15,7 @@ CASES = [  # d_model, heads, d_ff, vocab, seq, rows
     (512, 8, 512, 1602, 8, 3),    # 64 x 64 tiles for the unembedding
     (512, 8, 512, 3077, 12, 5),   # 128 x 64
     (64, 4, 128, 301, 256, 5),    # split-K
+    (512, 8, 128, 97, 64, 128),   # an odd k on register-staged 128 x 128 tiles (dU^T)
 ]
 
 
