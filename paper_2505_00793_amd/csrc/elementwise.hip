@@ -1424,22 +1424,22 @@ bool linreg_fits(int T, int rows, int vrows, int d) {
 }
 
 // Which form is the fastest, from the calls' times in us.  Registers against the
-// normal equations: 64 features x 256 rows T = 4 16 against 18, T = 8 29 against 23.
-// Staging starts faster (one launch) but costs more a phase (2 T + 1 phases), with
-// 16-byte loads up to about 200 features: 128 x 142 T = 1 14 against 18, T = 2 22
-// against 21; 176 x 32 T = 2 25 against 27; 192 x 32 T = 3 35 against 37, T = 4 44 each; 192 x 98 T = 2 29 against
-// 30, T = 3 39 against 37; 224 x 32 T = 4 50 against 52; 224 x 85 T = 3 43 each, T = 4
-// 54 against 53; 256 x 64 T = 8 92 against 120.  Its single-element
-// loads of other widths take 3 us more: 130 x 142 T = 1 21 against 18, 190 x 98 T = 1
-// 22 against 23.  Batches that LDS does not hold go through the normal equations at
-// any T (256 x 256, T = 1: 33 against 116 in one workgroup).
+// normal equations: 64 features x 256 rows T = 3 13 each, T = 4 16 against 14 (and a
+// workspace of checkpoints against one of matrices), T = 8 29 against 21.  Staging is
+// one launch instead of two but costs more a phase (2 T + 1 phases), up to 256
+// features: 160 x 32 T = 1 16 against 15; 192 x 32 T = 1 16 against 19, T = 2 26 each;
+// 224 x 32 T = 2 29 against 31, T = 3 40 against 39; 240 x 64 T = 4 53 each; 256 x 64
+// T = 8 95 against 115, T = 16 182 against 217.  Its single-element loads of other
+// widths take 3 us more a call: 190 x 32 T = 1 20 against 18.  Batches that LDS does not
+// hold go through the normal equations at any T (256 x 256, T = 1: 27 against 116 in
+// one workgroup).
 LinregForm linreg_form(int T, int rows, int vrows, int d) {
   const int r = std::max(rows, vrows);
   const bool vec = d % 4 == 0;
   if (vec && d <= LRR_MAXD && r <= LRR_MAXROWS && T <= LRR_MAXT) return LinregForm::Registers;
-  const int most = d > 224 ? LINREG_MAXT   // T up to which staging is faster
-                   : vec   ? (d < 184 ? 1 : d < 208 ? 2 : 3) + (d >= 168 && r <= 48 ? 1 : 0)
-                           : (d <= 64 || d >= 184 ? 1 : 0);
+  const int most = d > 224           ? LINREG_MAXT   // T up to which staging is taken
+                   : vec && d >= 184 ? (d < 208 ? 1 : 2)
+                                     : 0;
   return T <= most && r * lr_spitch(d) <= LR_STAGE ? LinregForm::Staged : LinregForm::Gram;
 }
 

@@ -7,7 +7,7 @@
 // of the sweep is one d x d matrix-vector product per phase, in one workgroup
 // (linreg_sweep_kernel).  Walking the batches themselves, 2 T + 1 of them, one
 // compute unit receives about 20 bytes a cycle: 130 features, 1000 rows, T = 3
-// took 620 us that way, 32 us this way.
+// took 620 us that way, 24 us this way.
 //
 // G, c and the whole sweep are float64.  Near a fit, or with features far from
 // zero mean, G theta - c cancels: from float32 matrices d eta lay up to six times as
@@ -37,9 +37,6 @@ struct GramArgs {
   const float* theta0;
   const float* eta;
   double* gsave;                  // [T][d] inner gradients
-  double* thetaT;                 // [d], for linreg_val_kernel
-  double* vpart;                  // its partial sums
-  unsigned* ticket;
   float* d_eta;
   float* val_loss;
 };
@@ -62,7 +59,6 @@ __global__ void __launch_bounds__(GR_THREADS) linreg_gram_kernel(GramArgs a) {
   }
   const int tj = ti + p;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (blockIdx.x == 0 && b == 0 && tid == 0) *a.ticket = 0u;
   const float* X = a.xs[b];
   const float* y = a.ys[b];
   const int rows = b < a.T ? a.rows : a.vrows;
@@ -123,6 +119,12 @@ __device__ __forceinline__ double quad_sum(double v) {   // over the four lanes 
   return v;
 }
 
+__device__ __forceinline__ double wave_sum_f64(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
 // The sweep: T inner steps, the seed at theta_T, T reverse steps, in one workgroup of
 // NT threads.  The rows 0 .. d - 1 of G, each ldg / 2 pieces of 16 bytes, are read as
 // one run of pieces, rps whole rows a step (NT pieces but for a last part of a row): a
@@ -132,6 +134,8 @@ __device__ __forceinline__ double quad_sum(double v) {   // over the four lanes 
 // in flight: a piece is replaced by the one R steps on, of the next phase's matrix at
 // the end.  The column sums go over a thread's steps, then over the rps rows of a step
 // through LDS (four lanes per column), in a fixed order.
+// The validation loss is theta^T (G theta - 2 c) + y^T y of its batch: what cancels there
+// is 1e-16 of |y|^2, less than the square of a float32 residual's rounding.
 constexpr int GR_RPS = 32;      // most rows a step
 constexpr int GR_XROWS = 512;   // rows of all steps, at most
 
@@ -139,6 +143,7 @@ template <int NT, int R>
 __global__ void __launch_bounds__(NT) linreg_sweep_kernel(GramArgs a) {
   __shared__ double x[GR_XROWS];           // the vector of this phase, zero past d
   __shared__ __attribute__((aligned(16))) double part[2 * NT];   // [rps][ldg]
+  __shared__ double red[NT / 64];
   const int tid = threadIdx.x;
   const int d = a.d, T = a.T, ldg = a.ldg, cp = ldg >> 1;
   const int rps = a.rps, span = rps * cp, rounds = a.rounds;
@@ -208,8 +213,11 @@ __global__ void __launch_bounds__(NT) linreg_sweep_kernel(GramArgs a) {
       }
     } else {
       if (p == T) {
-        if (a.val_loss && own) a.thetaT[j] = th;   // for linreg_val_kernel
-        tb = invv * (u - c);                       // the seed, dV/dtheta_T
+        if (a.val_loss) {
+          const double v = wave_sum_f64(own ? th * (u - 2.0 * c) : 0.0);
+          if ((tid & 63) == 0) red[tid >> 6] = v;
+        }
+        tb = invv * (u - c);   // the seed, dV/dtheta_T
       } else {
         eb = fma(-lam * gr, tb, eb);
         tb += inv * u;
@@ -219,61 +227,13 @@ __global__ void __launch_bounds__(NT) linreg_sweep_kernel(GramArgs a) {
     __syncthreads();
   }
   if (own) a.d_eta[j] = (float)eb;
-}
-
-__device__ __forceinline__ double wave_sum_f64(double v) {
+  if (a.val_loss && tid == 0) {
+    double v = a.G[((long)T * a.nr + d) * ldg + d];   // y^T y
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// The validation loss from its residuals: one wave per row, the workgroups' sums
-// added in order by the last one to finish.  A launch of its own also for small
-// batches: held in the sweep's registers from its start the batch made the sweep
-// longer by more, its unrolled code running once.
-__global__ void __launch_bounds__(256) linreg_val_kernel(GramArgs a) {
-  __shared__ double x[LINREG_MAXD];
-  __shared__ double red[4];
-  __shared__ bool last;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const float* X = a.xs[a.T];
-  const float* y = a.ys[a.T];
-  if (tid < a.d) x[tid] = a.thetaT[tid];
-  __syncthreads();
-  double ls = 0.0;
-  for (int r = blockIdx.x * 4 + w; r < a.vrows; r += gridDim.x * 4) {
-    constexpr int NV = LINREG_MAXD / 64;
-    float xr[NV];
-    double s = 0.0;
-    const float t = y[r];
-#pragma unroll
-    for (int n = 0; n < NV; ++n) xr[n] = X[(long)r * a.d + min(lane + 64 * n, a.d - 1)];
-#pragma unroll
-    for (int n = 0; n < NV; ++n)
-      if (lane + 64 * n < a.d) s = fma((double)xr[n], x[lane + 64 * n], s);
-    const double e = wave_sum_f64(s) - t;
-    ls = fma(e, e, ls);
+    for (int k = 0; k < NT / 64; ++k) v += red[k];
+    *a.val_loss = (float)((v < 0.0 ? 0.0 : v) / a.vrows);
   }
-  if (lane == 0) red[w] = ls;
-  __syncthreads();
-  if (tid == 0) {
-    __hip_atomic_store(a.vpart + blockIdx.x, (red[0] + red[1]) + (red[2] + red[3]),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence();
-    last = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
-           gridDim.x - 1;
-  }
-  __syncthreads();
-  if (!last || w != 0) return;
-  __threadfence();
-  double s = 0.0;
-  for (int k = lane; k < (int)gridDim.x; k += 64)
-    s += __hip_atomic_load(a.vpart + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  s = wave_sum_f64(s);
-  if (lane == 0) *a.val_loss = (float)(s / a.vrows);
 }
-
-constexpr int GR_VAL_BLOCKS = 256;
 
 // R: the steps of a phase, or a half or third .. of them where these are more than 13
 // (4 registers each).
@@ -292,10 +252,9 @@ inline int gram_rows(int d) { return (d + 1 + 15) / 16 * 16; }
 
 }  // namespace
 
-// The arrays of GramArgs in order, all of even length (16-byte aligned).
+// G, then the inner gradients.
 long linreg_gram_scratch_floats(int T, int d) {
-  return 2 * ((T + 1) * (long)gram_rows(d) * rup2(d + 1) + rup2((long)T * d) + rup2(d) +
-              GR_VAL_BLOCKS + 2);
+  return 2 * ((T + 1) * (long)gram_rows(d) * rup2(d + 1) + (long)T * d);
 }
 
 hipError_t linreg_gram_meta_grad(const float* theta0, const float* eta, const float* const* xs,
@@ -315,13 +274,10 @@ hipError_t linreg_gram_meta_grad(const float* theta0, const float* eta, const fl
   a.ldg = (int)rup2(d + 1);
   a.G = reinterpret_cast<double*>(scratch);
   a.gsave = a.G + (long)(T + 1) * a.nr * a.ldg;
-  a.thetaT = a.gsave + rup2((long)T * d);
-  a.vpart = a.thetaT + rup2(d);
-  a.ticket = reinterpret_cast<unsigned*>(a.vpart + GR_VAL_BLOCKS);
   a.theta0 = theta0; a.eta = eta; a.d_eta = d_eta; a.val_loss = val_loss;
   const int nt = a.nr / 16;
   hipLaunchKernelGGL(linreg_gram_kernel, dim3(nt * (nt + 1) / 2, T + 1), dim3(GR_THREADS), 0, s, a);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int threads = d <= 32 ? 128 : d <= 64 ? 512 : 1024;   // at least four per column
   a.rps = std::min(threads / (a.ldg / 2), GR_RPS);
@@ -329,14 +285,9 @@ hipError_t linreg_gram_meta_grad(const float* theta0, const float* eta, const fl
   a.rounds = (steps + 12) / 13;
   const int r = (steps + a.rounds - 1) / a.rounds;
   if (r * a.rounds * a.rps > GR_XROWS) return hipErrorInvalidValue;
-  e = threads == 128   ? launch_sweep<128>(a, r, s)
-      : threads == 512 ? launch_sweep<512>(a, r, s)
-                       : launch_sweep<1024>(a, r, s);
-  if (e != hipSuccess) return e;
-  if (val_loss)
-    hipLaunchKernelGGL(linreg_val_kernel, dim3(std::min((vrows + 3) / 4, GR_VAL_BLOCKS)),
-                       dim3(256), 0, s, a);
-  return hipGetLastError();
+  return threads == 128   ? launch_sweep<128>(a, r, s)
+         : threads == 512 ? launch_sweep<512>(a, r, s)
+                          : launch_sweep<1024>(a, r, s);
 }
 
 }  // namespace mfmg
