@@ -185,11 +185,13 @@ typedef struct {
    * with n_blocks.  1 keeps only the residual stream entering each block (and
    * its tangent) and recomputes the block's forward, with the tangent in dual
    * passes, at the start of that block's backward: one buffer set serves all
-   * blocks, dynamic memory is flat in n_blocks up to the block inputs
+   * blocks, or two where the second fits the dynamic memory reported for one (the
+   * buffers in that figure which bf16 operands and fused attention do without
+   * leave room), dynamic memory is flat in n_blocks up to the block inputs
    * (2 * 4 * rows * seq * d_model bytes per block), and each backward does one
-   * more block forward per block (its last residual product excepted).  The
-   * recomputation repeats the same kernels on the same inputs, so results are
-   * bit-identical to 0. */
+   * more block forward (its last residual product excepted) for every block but
+   * the last, or the last two.  The recomputation repeats the same kernels on the
+   * same inputs, so results are bit-identical to 0. */
   int block_remat;
 } mfmg_problem_desc;
 
@@ -200,11 +202,17 @@ typedef struct {
   size_t n_theta;              /* floats in theta */
   size_t n_opt_state;          /* floats in opt_state (0 for SGD) */
   size_t n_eta;                /* floats in eta (depends on T for EXAMPLE_WEIGHT_LOGITS) */
-  size_t workspace_bytes;      /* workspace mfmg_meta_grad needs at this T */
+  size_t workspace_bytes;      /* workspace mfmg_meta_grad needs at this T.  Linear
+                                  regression (one output, MSE, per-parameter rates, up
+                                  to 256 features, 1024 rows, 64 steps): checkpoints, or
+                                  from sizes where that is the faster form the T + 1
+                                  batches' (features + 1)^2 float64 matrices */
   size_t static_bytes;         /* part of it that lives through the whole call
                                   (theta checkpoints, adjoints, tangents) */
   size_t dynamic_bytes;        /* part of it reused by every inner step
-                                  (one step's activations); independent of T */
+                                  (one step's activations); independent of T.  For a
+                                  decoder every operand counts in both layouts, so with
+                                  bf16 operands this bounds what a call touches */
   size_t step_workspace_bytes; /* workspace mfmg_inner_step / mfmg_hvp_fwd_over_rev need */
 } mfmg_sizes;
 

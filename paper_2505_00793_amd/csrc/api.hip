@@ -93,7 +93,7 @@ struct mfmg_problem {
   // zero: the producers of activations and gradients write it with each row, and
   // zero_pads clears that of the weights' copies once per call.  (A 781-1000-515-37
   // ReLU network, 250 rows, T = 4: 1.92 ms with the ragged products on the
-  // register-staged kernel's single-element loads, 0.65 ms padded.)
+  // register-staged kernel's single-element loads, 0.57 ms padded.)
   int kx(int n) const { return (int)ld(n); }
 };
 

@@ -1802,7 +1802,7 @@ hipError_t launch_sized(const GemmOperands<T>& op, const Epi& epi, hipStream_t s
 // picks them.  The products take about the time they take from transposed copies (35 us
 // for the dual 512 x 2048 gradient over 4096 tokens, four k slices), and the copies
 // are not made: on the 4-block decoder at 4096 tokens some 250 transposes a
-// meta-gradient and a quarter of the activation epilogues' bytes (55.3 -> 51.1 ms).
+// meta-gradient and a quarter of the activation epilogues' bytes (55.2 -> 50.8 ms).
 template <int FLAGS>
 hipError_t launch_param_km(const GemmOperands<bf16_t>& op, const ParamOp<bf16_t>& epi,
                            hipStream_t s) {
@@ -1968,6 +1968,8 @@ hipError_t launch_qkv(const GemmOperands<bf16_t>& op, const QkvRopeOp& epi, hipS
 }
 }  // namespace
 
+// Decoders have at most 8192 tokens of 1024 dimensions a batch, so every operand is
+// within the direct-to-LDS loads' 2 GB (dma_ok) and no other path is needed.
 hipError_t gemm_qkv_rope(const GemmOperands<bf16_t>& op, int flags, const EpiQkvRope& e,
                          hipStream_t s) {
   if (op.batch != 1 || op.M <= 0 || op.N != 3 * 64 * e.H || e.S < 1 || op.M % e.S || !dma_ok(op))
