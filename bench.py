@@ -126,10 +126,10 @@ def algorithmic_bytes(cfg: W.Config, T: int):
 # 128 x 128 tiles on the direct-to-LDS path), for matching counter records.
 # (Regular expressions over the kernel name: flags, tile and epilogue; any k depth and stages.)
 CLASS_KERNEL = {
-    "dual_bwd_weight_gemm_reverse": r"gemm_nt_ws<7, 128, 128, \d+, \d+, mfmg::\(anonymous namespace\)::ParamOp",
-    "bwd_weight_gemm_update": r"gemm_nt_ws<1, 128, 128, \d+, \d+, mfmg::\(anonymous namespace\)::ParamOp",
-    "dual_fwd_gemm": r"gemm_nt_ws<7, 128, 128, \d+, \d+, mfmg::\(anonymous namespace\)::ActFwdOp",
-    "dual_bwd_data_gemm": r"gemm_nt_ws<7, 128, 128, \d+, \d+, mfmg::\(anonymous namespace\)::ActBwdOp",
+    "dual_bwd_weight_gemm_reverse": r"gemm_nt_ws<unsigned short, 7, 128, 128, \d+, mfmg::\(anonymous namespace\)::ParamOp",
+    "bwd_weight_gemm_update": r"gemm_nt_ws<unsigned short, 1, 128, 128, \d+, mfmg::\(anonymous namespace\)::ParamOp",
+    "dual_fwd_gemm": r"gemm_nt_ws<unsigned short, 7, 128, 128, \d+, mfmg::\(anonymous namespace\)::ActFwdOp",
+    "dual_bwd_data_gemm": r"gemm_nt_ws<unsigned short, 7, 128, 128, \d+, mfmg::\(anonymous namespace\)::ActBwdOp",
 }
 KERNEL_SOURCES = ["paper_2505_00793_amd/csrc/gemm.hip", "paper_2505_00793_amd/csrc/param_epi.h",
                   "paper_2505_00793_amd/csrc/kernels.h", "paper_2505_00793_amd/csrc/common.h"]
