@@ -1428,8 +1428,8 @@ bool linreg_fits(int T, int rows, int vrows, int d) {
 // workspace of checkpoints against one of matrices), T = 8 29 against 21.  Staging is
 // one launch instead of two but costs more a phase (2 T + 1 phases), up to 256
 // features: 160 x 32 T = 1 16 against 15; 192 x 32 T = 1 16 against 19, T = 2 26 each;
-// 224 x 32 T = 2 29 against 31, T = 3 40 against 39; 240 x 64 T = 4 53 each; 256 x 64
-// T = 8 95 against 115, T = 16 182 against 217.  Its single-element loads of other
+// 224 x 32 T = 2 29 against 31, T = 3 40 against 39; 240 x 64 T = 4 53 each, 240 x 72
+// T = 8 99 against 93; 256 x 72 T = 8 96 against 115, T = 16 185 against 219.  Its single-element loads of other
 // widths take 3 us more a call: 190 x 32 T = 1 20 against 18.  Batches that LDS does not
 // hold go through the normal equations at any T (256 x 256, T = 1: 27 against 116 in
 // one workgroup).
@@ -1437,8 +1437,8 @@ LinregForm linreg_form(int T, int rows, int vrows, int d) {
   const int r = std::max(rows, vrows);
   const bool vec = d % 4 == 0;
   if (vec && d <= LRR_MAXD && r <= LRR_MAXROWS && T <= LRR_MAXT) return LinregForm::Registers;
-  const int most = d > 224           ? LINREG_MAXT   // T up to which staging is taken
-                   : vec && d >= 184 ? (d < 208 ? 1 : 2)
+  const int most = d > 224 && (r <= 64 || (vec && d >= 252)) ? LINREG_MAXT   // T up to which
+                   : vec && d >= 184 ? (d < 208 ? 1 : 2)                     // staging is taken
                                      : 0;
   return T <= most && r * lr_spitch(d) <= LR_STAGE ? LinregForm::Staged : LinregForm::Gram;
 }

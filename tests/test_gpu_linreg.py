@@ -18,7 +18,8 @@ CASES = [
     # staged for few steps: both sides of the widths, rows and steps where the rule changes
     (16, 1024, 700, 1), (64, 257, 30, 1), (63, 256, 200, 1), (100, 182, 182, 1), (180, 116, 40, 1),
     (184, 98, 98, 1), (184, 99, 98, 1), (184, 98, 98, 2), (204, 98, 10, 1), (208, 85, 85, 2),
-    (224, 85, 85, 2), (224, 85, 86, 2), (224, 48, 30, 3), (190, 98, 5, 1), (225, 85, 85, 1),
+    (224, 85, 85, 2), (224, 85, 86, 2), (224, 48, 30, 3), (190, 98, 5, 1), (225, 85, 85, 1), (252, 75, 60, 3),
+    (248, 75, 60, 3),
 ]
 
 

@@ -14,7 +14,7 @@ def workspace(d, rows, T):
 
 
 @pytest.mark.parametrize("d,rows,T", [(64, 256, 4), (64, 256, 6), (4, 1, 1), (256, 64, 64),
-                                      (225, 70, 9), (184, 98, 1), (208, 85, 2), (224, 85, 2)])
+                                      (225, 64, 9), (252, 70, 9), (184, 98, 1), (208, 85, 2), (224, 85, 2)])
 def test_walked_batches_need_checkpoints_only(d, rows, T):
     assert workspace(d, rows, T) == 4 * (T + 1) * d
 
