@@ -674,8 +674,8 @@ __global__ void __launch_bounds__(1024) adam_reduce_kernel(const float* __restri
 // g = (2/N) X^T r, H v = (2/N) X^T rdot.
 // 512 threads.  The batches are used in the order of the sweep: the T
 // training batches, the validation batch, then the training batches again in
-// reverse.  Each fits in LDS (80 KB; linreg_form); it is staged there with rows padded to a
-// pitch of 16 (mod 32) floats, so that the four rows a quarter-wave reads with
+// reverse.  Each fits in LDS (80 KB; linreg_form); it is staged there with rows
+// padded to a pitch of 16 (mod 32) floats, so that the four rows a quarter-wave reads with
 // 16-byte accesses fall on distinct banks; the next batch's values are loaded
 // into registers while the current one is used, so the sweep waits on global
 // memory only for the first.  The checkpoints theta_t stay in LDS when
@@ -684,9 +684,9 @@ __global__ void __launch_bounds__(1024) adam_reduce_kernel(const float* __restri
 // groups x 32 row groups per pass with an ordered sum of the 32 partials.
 // ------------------------------------------------------------------------------------
 constexpr int LR_MAXD = LINREG_MAXD;
-constexpr int LR_MAXR = LINREG_MAXR;
 constexpr int LR_THREADS = 512;
-constexpr int LR_YPT = LR_MAXR / LR_THREADS;   // targets per thread
+constexpr int LR_STAGED_D = 184, LR_STAGED_ROWS = 98;   // least width, most rows of a staged batch
+static_assert(LR_STAGED_ROWS <= LR_THREADS, "one target per thread");
 constexpr int LR_STAGE = 20480;  // floats of one batch staged in LDS, rows padded (80 KB)
 constexpr int LR_PF = LR_STAGE / LR_THREADS;  // prefetched floats per thread (n <= LR_STAGE)
 constexpr int LR_PF4 = LR_PF / 4;             // prefetched 16-byte groups per thread
@@ -708,10 +708,11 @@ struct LinregArgs {
 };
 
 // Padded row pitch of a staged batch: d rounded up to 4, then to 16 (mod 32).
-__host__ __device__ __forceinline__ int lr_spitch(int d) {
+__host__ __device__ __forceinline__ constexpr int lr_spitch(int d) {
   const int p = (d + 3) & ~3;
   return p + ((16 - (p & 31)) & 31);
 }
+static_assert((LR_STAGED_ROWS + 1) * lr_spitch(LR_STAGED_D) > LR_STAGE, "no batch has more rows");
 
 // Batch k of the sweep (k = 0 .. 2T).
 struct LrBatch {
@@ -726,13 +727,13 @@ __device__ __forceinline__ LrBatch lr_batch(const LinregArgs& a, int k) {
 }
 
 // Registers holding one batch on its way to LDS: 16-byte group tid + u *
-// LR_THREADS of X (VEC), or element tid + u * LR_THREADS, and y[tid], ...  The
+// LR_THREADS of X (VEC), or element tid + u * LR_THREADS, and y[tid].  The
 // loads are unconditional (an index past the end reads the last element) so
 // that a register is never both cleared and loaded: the compiler would then
 // wait for every load in flight.
 struct LrRegs {
   float x[LR_PF];   // VEC: group u in x[4u .. 4u + 3]
-  float y[LR_YPT];
+  float y;
 };
 template <bool VEC>
 __device__ __forceinline__ void lr_load(const LrBatch& b, int d, LrRegs& g) {
@@ -749,8 +750,7 @@ __device__ __forceinline__ void lr_load(const LrBatch& b, int d, LrRegs& g) {
 #pragma unroll
     for (int u = 0; u < LR_PF; ++u) g.x[u] = b.X[min(tid + u * LR_THREADS, n - 1)];
   }
-#pragma unroll
-  for (int v = 0; v < LR_YPT; ++v) g.y[v] = b.y[min(tid + v * LR_THREADS, b.rows - 1)];
+  g.y = b.y[min(tid, b.rows - 1)];
 }
 // Registers -> LDS (padded rows; the padding columns stay zero).  Callers
 // synchronise before (the previous batch's readers are done) and after.
@@ -758,9 +758,7 @@ template <bool VEC>
 __device__ __forceinline__ void lr_commit(const LrBatch& b, int d, const LrRegs& g, float* stage,
                                           float* ys) {
   const int tid = threadIdx.x;
-#pragma unroll
-  for (int v = 0; v < LR_YPT; ++v)
-    if (tid + v * LR_THREADS < b.rows) ys[tid + v * LR_THREADS] = g.y[v];
+  if (tid < b.rows) ys[tid] = g.y;
   const int n = b.rows * d, P = lr_spitch(d);
   // element i = row * d + col goes to row * P + col; row and col advance by the
   // elements of one step without a division
@@ -927,7 +925,7 @@ __global__ void __launch_bounds__(LR_THREADS) linreg_kernel(LinregArgs a) {
   __shared__ __attribute__((aligned(16))) float th[LR_MAXD], vv[LR_MAXD];
   __shared__ float tb[LR_MAXD], lam[LR_MAXD], eb[LR_MAXD];
   __shared__ float gs[LR_MAXD], hs[LR_MAXD];
-  __shared__ float r[LR_MAXR], rd[LR_MAXR], ys[LR_MAXR];
+  __shared__ float r[LR_STAGED_ROWS], rd[LR_STAGED_ROWS], ys[LR_STAGED_ROWS];
   constexpr int NPART = LR_CRG * 4 * LR_CG;
   __shared__ __attribute__((aligned(16))) float part[NPART], part2[NPART];
   __shared__ float red[LR_THREADS / 64];
@@ -1419,8 +1417,8 @@ hipError_t adam_reduce(const float* partial, const int* block_offsets, int n_lay
 }
 
 bool linreg_fits(int T, int rows, int vrows, int d) {
-  return T >= 1 && T <= LINREG_MAXT && d >= 1 && d <= LR_MAXD && rows >= 1 && rows <= LR_MAXR &&
-         vrows >= 1 && vrows <= LR_MAXR;
+  return T >= 1 && T <= LINREG_MAXT && d >= 1 && d <= LR_MAXD && rows >= 1 && rows <= LINREG_MAXR &&
+         vrows >= 1 && vrows <= LINREG_MAXR;
 }
 
 // Which form is the fastest, from the calls' times in us.  Registers against the
@@ -1429,17 +1427,17 @@ bool linreg_fits(int T, int rows, int vrows, int d) {
 // one launch instead of two but costs more a phase (2 T + 1 phases), up to 256
 // features: 160 x 32 T = 1 16 against 15; 192 x 32 T = 1 16 against 19, T = 2 26 each;
 // 224 x 32 T = 2 29 against 31, T = 3 40 against 39; 240 x 64 T = 4 53 each, 240 x 72
-// T = 8 99 against 93; 256 x 72 T = 8 96 against 115, T = 16 185 against 219.  Its single-element loads of other
-// widths take 3 us more a call: 190 x 32 T = 1 20 against 18.  Batches that LDS does not
-// hold go through the normal equations at any T (256 x 256, T = 1: 27 against 116 in
-// one workgroup).
+// T = 8 99 against 93; 256 x 72 T = 8 96 against 115, T = 16 185 against 219.  Its
+// single-element loads of other widths take 3 us more a call: 190 x 32 T = 1 20
+// against 18.  Batches that LDS does not hold go through the normal equations at any
+// T (256 x 256, T = 1: 27 against 116 in one workgroup).
 LinregForm linreg_form(int T, int rows, int vrows, int d) {
   const int r = std::max(rows, vrows);
   const bool vec = d % 4 == 0;
   if (vec && d <= LRR_MAXD && r <= LRR_MAXROWS && T <= LRR_MAXT) return LinregForm::Registers;
-  const int most = d > 224 && (r <= 64 || (vec && d >= 252)) ? LINREG_MAXT   // T up to which
-                   : vec && d >= 184 ? (d < 208 ? 1 : 2)                     // staging is taken
-                                     : 0;
+  int most = 0;   // T up to which staging is taken
+  if (d > 224 && (r <= 64 || (vec && d >= 252))) most = LINREG_MAXT;
+  else if (vec && d >= LR_STAGED_D) most = d < 208 ? 1 : 2;
   return T <= most && r * lr_spitch(d) <= LR_STAGE ? LinregForm::Staged : LinregForm::Gram;
 }
 
